@@ -694,12 +694,20 @@ __global__ __launch_bounds__(BLOCK) void shared_scan_kernel(const BatchDev batch
     if (lane < tail - head) finish_entry((head + lane) & (uint32_t)(kQueueCap - 1));
     if (bad_group) set_status(status, CRYSTAL_ERANGE);
     if (p.scalar) {
+        // Wave w sums the lanes of queries w, w + W, ...; then one instruction
+        // adds every query's total, a lane each.  The outputs of a served
+        // batch are neighbours, and adds to one memory line serialise: with an
+        // add per (workgroup, query) a 16-query pass of 768 workgroups queued
+        // 12,288 of them on one line, 109 us for 7.5M rows.
         __syncthreads();  // every wave's adds are done
-        if (threadIdx.x < kWave) {
-            for (int q = 0; q < b.n_queries; ++q) {
-                const uint64_t t = wave_sum_u64(acc[q][lane]);
-                if (lane == 0 && t) atomic_add_u64(b.out[q], t);
-            }
+        for (int q = threadIdx.x / kWave; q < b.n_queries; q += T::WAVES) {
+            const uint64_t t = wave_sum_u64(acc[q][lane]);
+            if (lane == 0) acc[q][0] = t;
+        }
+        __syncthreads();
+        if ((int)threadIdx.x < b.n_queries) {
+            const uint64_t t = acc[threadIdx.x][0];
+            if (t) atomic_add_u64(b.out[threadIdx.x], t);
         }
     }
 }

@@ -321,3 +321,26 @@ def test_ranked_table_in_a_late_join(serving, block, ipt):
             assert np.array_equal(outs[q].cpu().numpy(), star_oracle(t, consts[q])[0]), q
     finally:
         cx.tune_reset()
+
+
+# ------------------------------------------------------- scalar batch totals --
+@pytest.mark.parametrize("block,ipt,nq", [(64, 4, 16), (64, 4, 1), (128, 8, 7), (512, 8, 16), (1024, 4, 9)])
+def test_scalar_totals_with_neighbouring_outputs(serving, block, ipt, nq):
+    """A workgroup adds its totals with one instruction, a lane per query:
+    fewer waves than queries, more waves than queries, and outputs that share
+    memory lines, added to what they held."""
+    announce("shared scalar totals", block, ipt, nq)
+    t, sv = serving
+    f = q11_fact_of(t)
+    rng = np.random.default_rng(block + nq)
+    consts = [datagen.random_q11_constants(rng) for _ in range(nq)]
+    outs = torch.arange(nq, dtype=torch.int64, device="cuda")
+    cx.tune_set(cx.K_SHARED_SCAN_SCALAR, block, ipt, 0)
+    try:
+        cx.check_status(sv.run_q11_batch(consts, [outs[q:q + 1] for q in range(nq)]))
+    finally:
+        cx.tune_reset()
+    cx.check_status(sv.status)
+    got = outs.cpu().numpy()
+    for q, (year, d, qm) in enumerate(consts):
+        assert int(got[q]) - q == q11_oracle(f, year, (d, d + 2), qm), (q, consts[q])
