@@ -49,6 +49,15 @@ hipError_t fill_u64(uint64_t *p, int64_t n, uint64_t value, hipStream_t s);
 // zero the slots slots[0..count) (each len words) of base in one launch; count <= kMaxSlots
 constexpr int kMaxSlots = 64;
 hipError_t zero_slots(uint64_t *base, int64_t len, const int32_t *slots, int count, hipStream_t s);
+// copy the word ranges r[0..count) of src to the same places of dst, and *status to *status_copy, in one launch
+struct WordRanges {
+    int32_t count;
+    struct {
+        int64_t at, len;
+    } r[kMaxSlots];
+};
+hipError_t copy_ranges(const uint64_t *src, uint64_t *dst, const WordRanges &ranges, const int32_t *status,
+                       int32_t *status_copy, hipStream_t s);
 hipError_t fill_u32(uint32_t *p, int64_t n, uint32_t value, hipStream_t s);
 // Zero two separate 64-bit words with one launch.
 hipError_t zero_pair(uint64_t *a, uint64_t *b, hipStream_t s);

@@ -76,6 +76,32 @@ hipError_t zero_slots(uint64_t *base, int64_t len, const int32_t *slots, int cou
     return hipGetLastError();
 }
 
+// The results a served step completes, written straight into pinned host
+// memory (dst and status_copy).  A copy call per query cost about 10 us each
+// on the stream: a step that completes 32 queries went from 33 calls to one
+// launch, bound by the 900 KB it sends over PCIe.
+__global__ __launch_bounds__(256) void copy_ranges_kernel(const uint64_t *__restrict__ src, uint64_t *__restrict__ dst,
+                                                          WordRanges ranges, const int32_t *__restrict__ status,
+                                                          int32_t *__restrict__ status_copy) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i0 == 0) *status_copy = *status;
+    for (int k = 0; k < ranges.count; ++k) {
+        const int64_t at = ranges.r[k].at;
+        for (int64_t i = i0; i < ranges.r[k].len; i += stride) dst[at + i] = src[at + i];
+    }
+}
+
+hipError_t copy_ranges(const uint64_t *src, uint64_t *dst, const WordRanges &ranges, const int32_t *status,
+                       int32_t *status_copy, hipStream_t s) {
+    if (ranges.count < 0 || ranges.count > kMaxSlots) return hipErrorInvalidValue;
+    int64_t longest = 1;
+    for (int k = 0; k < ranges.count; ++k) longest = ranges.r[k].len > longest ? ranges.r[k].len : longest;
+    hipLaunchKernelGGL(copy_ranges_kernel, dim3((unsigned)fill_grid(longest)), dim3(256), 0, s, src, dst, ranges,
+                       status, status_copy);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------- selection --
 // Tile = BlockLoad -> BlockPred -> BlockScan of the match counts -> the tile's
 // output offset -> BlockShuffle into LDS (matches in input order within the

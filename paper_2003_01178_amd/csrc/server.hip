@@ -36,6 +36,8 @@
 
 namespace crystal {
 
+static_assert(CRYSTAL_SERVER_MAX_TEMPLATES * CRYSTAL_MAX_BATCH <= kMaxSlots, "one range per slot");
+
 using Clock = std::chrono::steady_clock;
 
 static int64_t now_ns() {
@@ -88,7 +90,9 @@ struct Server {
     int64_t clock = 0;
     hipStream_t stream = nullptr;
     bool own_stream = false;
-    int64_t *pinned = nullptr;        // host copies of slot outputs, then of the status word
+    int64_t *pinned = nullptr;        // host copies of slot outputs (out_words), then of the status word
+    int64_t *pinned_dev = nullptr;    // the same memory, as the device addresses it
+    int64_t out_words = 0;
     int32_t *status = nullptr;        // device status word (inside the workspace)
     int32_t *pinned_status = nullptr; // its host copy, taken in every step that completes a query
     std::vector<std::vector<Slot>> slots;
@@ -114,11 +118,8 @@ struct Server {
         off += n_groups(t) * s;
         return (int64_t *)cfg.workspace + 2 + off;  // first 16 bytes: status word
     }
-    int64_t *pinned_out(int t, int s) const {
-        int64_t off = 0;
-        for (int u = 0; u < t; ++u) off += n_groups(u) * cfg.slots_per_template;
-        return pinned + off + n_groups(t) * s;
-    }
+    // host copies lie as the slots do
+    int64_t *pinned_out(int t, int s) const { return pinned + (slot_out(t, s) - slot_out(0, 0)); }
 
     void fail(crystal_status st) {
         std::lock_guard<std::mutex> lk(mu);
@@ -194,23 +195,26 @@ struct Server {
                 if (--sl.steps_left == 0) {
                     step.completing.push_back({t, q, sl.ticket});
                     masks_dirty[t][0] = true;  // its bit must stop matching
-                    if (!cfg.fake_executor &&
-                        hipMemcpyAsync(pinned_out(t, q), slot_out(t, q), n_groups(t) * 8, hipMemcpyDeviceToHost,
-                                       stream) != hipSuccess) {
-                        fail(CRYSTAL_EHIP);
-                        return false;
-                    }
                 }
             }
         }
         if (!any) return false;
-        // The status word is sticky (the first device error stays), so its
-        // copy after a step's kernels covers every step up to this one; it is
-        // taken only where results are released.
-        if (!cfg.fake_executor && !step.completing.empty() &&
-            hipMemcpyAsync(pinned_status, status, 4, hipMemcpyDeviceToHost, stream) != hipSuccess) {
-            fail(CRYSTAL_EHIP);
-            return false;
+        // The finished queries' outputs, and the status word, go to the host
+        // copies in one launch.  The status word is sticky (the first device
+        // error stays), so its copy after a step's kernels covers every step up
+        // to this one; it is taken only where results are released.
+        if (!cfg.fake_executor && !step.completing.empty()) {
+            WordRanges done = {};
+            for (const Completion &c : step.completing) {
+                auto &r = done.r[done.count++];  // at most kMaxSlots: every slot of every template
+                r.at = slot_out(c.t, c.q) - slot_out(0, 0);
+                r.len = n_groups(c.t);
+            }
+            if (copy_ranges((const uint64_t *)slot_out(0, 0), (uint64_t *)pinned_dev, done, status,
+                            (int32_t *)(pinned_dev + out_words), stream) != hipSuccess) {
+                fail(CRYSTAL_EHIP);
+                return false;
+            }
         }
         clock = (clock + 1) % n_segments;
         ++steps;
@@ -448,14 +452,19 @@ crystal_status crystal_server_create(const crystal_server_config *cfg, crystal_s
         } else {
             s.own_stream = true;
         }
-        size_t host_bytes = 0;
-        for (int t = 0; t < cfg->n_templates; ++t) host_bytes += (size_t)s.n_groups(t) * 8 * cfg->slots_per_template;
-        if (hipHostMalloc((void **)&s.pinned, host_bytes + 8, hipHostMallocDefault) != hipSuccess) {
+        for (int t = 0; t < cfg->n_templates; ++t) s.out_words += s.n_groups(t) * cfg->slots_per_template;
+        if (hipHostMalloc((void **)&s.pinned, (size_t)s.out_words * 8 + 8, hipHostMallocDefault) != hipSuccess) {
             if (s.own_stream) (void)hipStreamDestroy(s.stream);
             delete h;
             return CRYSTAL_EHIP;
         }
-        s.pinned_status = (int32_t *)((char *)s.pinned + host_bytes);
+        if (hipHostGetDevicePointer((void **)&s.pinned_dev, s.pinned, 0) != hipSuccess) {
+            (void)hipHostFree(s.pinned);
+            if (s.own_stream) (void)hipStreamDestroy(s.stream);
+            delete h;
+            return CRYSTAL_EHIP;
+        }
+        s.pinned_status = (int32_t *)(s.pinned + s.out_words);
         *s.pinned_status = CRYSTAL_OK;
         s.status = (int32_t *)cfg->workspace;
         if (fill_u32((uint32_t *)s.status, 4, 0u, s.stream) != hipSuccess) {
