@@ -8,7 +8,7 @@ namespace crystal {
 
 static constexpr uint64_t kEmptySlot = (uint64_t)(uint32_t)kEmptyKey;  // {EMPTY, 0}
 
-static inline int64_t direct_bitmap_words(int64_t span) {
+__host__ __device__ static inline int64_t direct_bitmap_words(int64_t span) {
     int64_t w = (span + 31) / 32;
     return (w + 63) / 64 * 64;
 }
@@ -287,7 +287,12 @@ struct ProbeRegs {
 // item, keep a per-thread sum and match count, BlockAggregate, and add the
 // workgroup's totals with two 64-bit atomics.  MODE 0: linear probing in
 // global memory; MODE 1: linear probing in a copy of the table staged in LDS
-// once per workgroup; MODE 2: direct table.  PP: probe rows carry a payload
+// once per workgroup; MODE 2: direct table; MODE 3: direct table whose bitmap
+// is staged, MODE 4: whose payloads are staged too.  A gather from L2 moves a
+// 128-byte line to the CU, so 2^27 probes that make one take about 520 us and
+// two about 1,000: with the bitmap staged, 2^20 keys went from 1,094 to 620 us
+// and 2^16 from 590 to 518; with all of it staged, 2^15 keys from 527 to 95 us
+// and 2^10 from 235 to 94 (the keys' own 512 MB take 83).  PP: probe rows carry a payload
 // (pp is not null), a separate instance so that the payload registers exist
 // only when used.
 template <int BLOCK, int IPT, int MODE, bool PP>
@@ -301,12 +306,19 @@ __global__ __launch_bounds__(BLOCK) void ht_probe_kernel(DevTable t, const int32
     __shared__ uint64_t red[T::WAVES];
     const v2i *slots = t.slots;
     if constexpr (MODE == 1) {
-        // stage the whole table: capacity * 8 bytes, 16 bytes per load
-        const int64_t n16 = ((int64_t)t.mask + 1) / 2;
-        const v4i *src = reinterpret_cast<const v4i *>(t.slots);
-        for (int64_t i = threadIdx.x; i < n16; i += BLOCK) lds_raw[i] = src[i];
+        // stage the whole table
+        copy_to_lds<BLOCK>(reinterpret_cast<const uint32_t *>(t.slots), reinterpret_cast<uint32_t *>(lds_raw),
+                           2 * ((int)t.mask + 1));
         __syncthreads();
         slots = reinterpret_cast<const v2i *>(lds_raw);
+    }
+    const uint32_t *lds_words = reinterpret_cast<const uint32_t *>(lds_raw);
+    const int bitmap_words = (int)direct_bitmap_words(t.span);
+    if constexpr (MODE == 3 || MODE == 4) {
+        // stage the bitmap, and the payloads, which follow it in memory
+        copy_to_lds<BLOCK>(t.bitmap, reinterpret_cast<uint32_t *>(lds_raw),
+                           bitmap_words + (MODE == 4 ? (int)t.span : 0));
+        __syncthreads();
     }
     uint64_t sum = 0, cnt = 0;
     // one tile: the probes of its (already loaded) keys
@@ -316,7 +328,7 @@ __global__ __launch_bounds__(BLOCK) void ht_probe_kernel(DevTable t, const int32
         const uint32_t valid = valid_mask<BLOCK, IPT>(base, n);
         uint32_t hit = 0;
         int32_t pay[IPT];
-        if constexpr (MODE == 2) {
+        if constexpr (MODE >= 2) {
             // direct table: every item's presence word at once, then the payloads of the hits
             uint32_t word[IPT], ok = 0;
 #pragma unroll
@@ -324,7 +336,10 @@ __global__ __launch_bounds__(BLOCK) void ht_probe_kernel(DevTable t, const int32
                 const uint32_t off = (uint32_t)key[k] - (uint32_t)t.key_min;
                 const bool in = ((valid >> k) & 1u) && (int64_t)off < t.span;
                 ok |= (uint32_t)in << k;
-                word[k] = t.bitmap[in ? (off >> 5) : 0u];
+                if constexpr (MODE == 2)
+                    word[k] = t.bitmap[in ? (off >> 5) : 0u];
+                else
+                    word[k] = lds_words[in ? (off >> 5) : 0u];
             }
 #pragma unroll
             for (int k = 0; k < IPT; ++k) {
@@ -334,7 +349,12 @@ __global__ __launch_bounds__(BLOCK) void ht_probe_kernel(DevTable t, const int32
 #pragma unroll
             for (int k = 0; k < IPT; ++k) {
                 const uint32_t off = (uint32_t)key[k] - (uint32_t)t.key_min;
-                pay[k] = t.has_payload && ((hit >> k) & 1u) ? t.payload[off] : 0;
+                if constexpr (MODE == 4) {
+                    const uint32_t x = lds_words[bitmap_words + (((hit >> k) & 1u) ? off : 0u)];
+                    pay[k] = ((hit >> k) & 1u) ? (int32_t)x : 0;
+                } else {
+                    pay[k] = t.has_payload && ((hit >> k) & 1u) ? t.payload[off] : 0;
+                }
             }
         } else if constexpr (MODE == 0) {
             // table in global memory: one probe sequence per item (issuing every
@@ -394,7 +414,7 @@ __global__ __launch_bounds__(BLOCK) void ht_probe_kernel(DevTable t, const int32
                 }
             }
         }
-        if constexpr (MODE == 1) {
+        if constexpr (MODE != 0) {
             // pay[k] is 0 for misses: the sum needs no per-item branch
 #pragma unroll
             for (int k = 0; k < IPT; ++k) {
@@ -453,10 +473,17 @@ __global__ __launch_bounds__(BLOCK) void ht_probe_kernel(DevTable t, const int32
 }
 
 template <int BLOCK, int IPT, bool PP>
-static hipError_t probe_launch(const crystal_ht &ht, const DevTable &t, bool stage, int64_t table_bytes,
+static hipError_t probe_launch(const crystal_ht &ht, const DevTable &t, bool stage, bool all, int64_t table_bytes,
                                int64_t grid, const int32_t *fk, const int32_t *pp, int64_t n, uint64_t *out,
                                uint64_t *cnt, int64_t n_tiles, hipStream_t s) {
-    if (ht.kind == CRYSTAL_HT_DIRECT) {
+    if (ht.kind == CRYSTAL_HT_DIRECT && stage) {
+        auto fn = all ? ht_probe_kernel<BLOCK, IPT, 4, PP> : ht_probe_kernel<BLOCK, IPT, 3, PP>;
+        hipError_t e = hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)table_bytes);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(BLOCK), (size_t)table_bytes, s, t, fk, pp, n,
+                           out, cnt, n_tiles);
+    } else if (ht.kind == CRYSTAL_HT_DIRECT) {
         hipLaunchKernelGGL((ht_probe_kernel<BLOCK, IPT, 2, PP>), dim3((unsigned)grid), dim3(BLOCK), 0, s,
                            t, fk, pp, n, out, cnt, n_tiles);
     } else if (stage) {
@@ -480,14 +507,274 @@ static hipError_t probe_t(const LaunchCfg &cfg_in, const crystal_ht &ht, const i
     const int64_t n_tiles = (n + T::ITEMS - 1) / T::ITEMS;
     const DevTable t = to_dev(ht);
     LaunchCfg cfg = cfg_in;
-    const int64_t table_bytes = ht.kind == CRYSTAL_HT_LINEAR ? ht.capacity * 8 : 0;
-    const bool stage = ht.kind == CRYSTAL_HT_LINEAR && table_bytes <= device_lds_per_block() - 4096;
+    // staged in LDS: a linear table, a direct table, or only its bitmap
+    const int64_t lds_max = device_lds_per_block() - 4096;
+    int64_t table_bytes = ht.capacity * 8;
+    bool all = false;
+    if (ht.kind == CRYSTAL_HT_DIRECT) {
+        table_bytes = direct_bitmap_words(ht.capacity) * 4;
+        const int64_t with_payload = table_bytes + (ht.capacity * 4 + 15) / 16 * 16;
+        all = ht.has_payload && with_payload <= lds_max;
+        if (all) table_bytes = with_payload;
+    }
+    const bool stage = table_bytes <= lds_max;
     if (stage && cfg.grid_per_cu <= 0) cfg.grid_per_cu = 1;  // stage once per resident workgroup
     const int64_t grid = grid_for(n_tiles, cfg);
     if (grid == 0) return hipSuccess;
     if (pp)
-        return probe_launch<BLOCK, IPT, true>(ht, t, stage, table_bytes, grid, fk, pp, n, out, cnt, n_tiles, s);
-    return probe_launch<BLOCK, IPT, false>(ht, t, stage, table_bytes, grid, fk, pp, n, out, cnt, n_tiles, s);
+        return probe_launch<BLOCK, IPT, true>(ht, t, stage, all, table_bytes, grid, fk, pp, n, out, cnt, n_tiles, s);
+    return probe_launch<BLOCK, IPT, false>(ht, t, stage, all, table_bytes, grid, fk, pp, n, out, cnt, n_tiles, s);
+}
+
+// ----------------------------------------------------------- sliced probe --
+// Query Q4 on a table larger than an XCD's 4 MB L2, where a probe costs a
+// 128-byte line from the last-level cache (2^20 build keys, a 16 MB table:
+// 9 TB/s of lines, 1,767 us for 2^27 probes).
+//
+// Slices: the table is dealt to 2^LG slices in pieces of at least 8 KB, and a
+// workgroup probes only the keys whose home lies in its slice; the workgroups
+// of every slice read all the keys.  Consecutive workgroups run on the eight
+// XCDs in turn, so an XCD's L2 sees one slice of the table (only speed depends
+// on that).  Each wave compacts the keys of its slice into an LDS queue and
+// probes them four per lane.  The keys are loaded without the non-temporal
+// hint, so that their second and later reads hit the last-level cache.
+// Retries (linear probing): a lane reads its home slot and the next with one
+// 16-byte load; keys those do not decide wait in a second queue until 64 are
+// there, so a wave does not follow its longest chain.
+//
+// Measured, 2^27 probes without payload, before -> now: 8 MB table 1,218 ->
+// 782 us, 16 MB 1,767 -> 962 us, 32 MB 2,110 -> 1,330 us.  What bounds it is
+// the line each probe moves from L2 to the CU (a table within L2 takes 600 us)
+// and the compaction of the keys, about 45 us per slice.
+template <int BLOCK, int IPT, int KIND, bool PP, int LG>
+__global__ __launch_bounds__(BLOCK) void ht_probe_sliced_kernel(DevTable t, const int32_t *__restrict__ fk,
+                                                                const int32_t *__restrict__ pp, int64_t n,
+                                                                uint64_t *__restrict__ out_sum,
+                                                                uint64_t *__restrict__ out_cnt, int64_t n_tiles) {
+    using T = TileShape<BLOCK, IPT>;
+    constexpr bool kLinear = KIND == CRYSTAL_HT_LINEAR;
+    constexpr int D = 4;                       // keys a lane probes at a time
+    constexpr uint32_t kQ = 2 * D * kWave;     // slice queue: fewer than D * 64 left over, then at most D * 64 more
+    constexpr uint32_t kR = 2 * kWave;         // retry queue: fewer than 64 left over, then at most 64 more
+    constexpr uint32_t kPieceLg = 11;          // direct: 2^11 payloads, 8 KB
+    __shared__ int32_t q_key[T::WAVES][kQ];
+    __shared__ int32_t q_pv[PP ? T::WAVES : 1][PP ? kQ : 1];
+    __shared__ int32_t r_key[kLinear ? T::WAVES : 1][kR];
+    __shared__ uint32_t r_slot[kLinear ? T::WAVES : 1][kR];
+    __shared__ int32_t r_pv[kLinear && PP ? T::WAVES : 1][kLinear && PP ? kR : 1];
+    __shared__ uint64_t red[2][T::WAVES];
+    const int w = (int)threadIdx.x / kWave;
+    int32_t *my_key = q_key[w], *my_pv = q_pv[PP ? w : 0];
+    int32_t *my_rkey = r_key[kLinear ? w : 0], *my_rpv = r_pv[kLinear && PP ? w : 0];
+    uint32_t *my_rslot = r_slot[kLinear ? w : 0];
+    const uint32_t lane = lane_id();
+    const uint32_t slice = blockIdx.x & ((1u << LG) - 1u);
+    uint32_t head = 0, tail = 0, rhead = 0, rtail = 0;  // queue cursors, equal in every lane of the wave
+    uint64_t sum = 0, cnt = 0;
+
+    // Bits [24 - LG, 24) of the hash product, which the low 24 bits of both
+    // factors determine (a full-rate multiply): they are slot bits, the lowest
+    // of them bit 24 - LG - shift, at least 10 for the tables of 2^20 slots or
+    // more that take this path.
+    auto slice_of = [&](int32_t k) -> uint32_t {
+        if constexpr (kLinear)
+            return __builtin_amdgcn_ubfe(__umul24((uint32_t)k, 2654435761u & 0xffffffu), 24 - LG, LG);
+        else
+            return __builtin_amdgcn_ubfe((uint32_t)k - (uint32_t)t.key_min, kPieceLg, LG);
+    };
+    // the oldest `count` (at most 64) retries, one per lane, slot by slot to their end
+    auto retry = [&](uint32_t count) {
+        if (lane < count) {
+            const uint32_t i = (rhead + lane) & (kR - 1u);
+            const int32_t k = my_rkey[i];
+            uint32_t s = my_rslot[i];
+            for (uint32_t step = 0; step <= t.mask; ++step) {
+                const v2i e = t.slots[s];
+                if (e.x == k) {
+                    sum += (uint64_t)(int64_t)e.y;
+                    if constexpr (PP) sum += (uint64_t)(int64_t)my_rpv[i];
+                    ++cnt;
+                    break;
+                }
+                if (e.x == kEmptyKey) break;
+                s = (s + 1u) & t.mask;
+            }
+        }
+        rhead += count;
+    };
+    // probe the oldest `count` (at most D * 64) keys of the slice queue
+    auto drain = [&](uint32_t count) {
+        int32_t key[D], pv[PP ? D : 1];
+        uint32_t ok = 0;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const uint32_t j = (uint32_t)d * kWave + lane;
+            const uint32_t i = (head + j) & (kQ - 1u);
+            key[d] = my_key[i];
+            if constexpr (PP) pv[d] = my_pv[i];
+            ok |= (uint32_t)(j < count) << d;
+        }
+        head += count;
+        if constexpr (kLinear) {
+            typedef int32_t v4i_8 __attribute__((ext_vector_type(4), aligned(8)));
+            uint32_t slot[D];
+            v4i e[D];
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                if (key[d] == kEmptyKey) ok &= ~(1u << d);
+                slot[d] = ((ok >> d) & 1u) ? hash_slot(key[d], t.shift) : 0u;
+                // the last slot is read as the second of its pair
+                const uint32_t at = slot[d] < t.mask ? slot[d] : t.mask - 1u;
+                e[d] = *reinterpret_cast<const v4i_8 *>(t.slots + at);
+            }
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const bool valid = (ok >> d) & 1u;
+                const bool last = slot[d] == t.mask;
+                const int32_t k0 = last ? e[d].z : e[d].x, p0 = last ? e[d].w : e[d].y;
+                const bool h0 = k0 == key[d];
+                const bool go = !h0 && k0 != kEmptyKey;
+                const bool h1 = go && !last && e[d].z == key[d];
+                if (valid && (h0 || h1)) {
+                    sum += (uint64_t)(int64_t)(h0 ? p0 : e[d].w);
+                    if constexpr (PP) sum += (uint64_t)(int64_t)pv[d];
+                    ++cnt;
+                }
+                const bool again = valid && go && !h1 && (last || e[d].z != kEmptyKey);
+                const uint64_t m = ballot(again);
+                if (again) {
+                    const uint32_t i = (rtail + count_below(m)) & (kR - 1u);
+                    my_rkey[i] = key[d];
+                    my_rslot[i] = (slot[d] + (last ? 1u : 2u)) & t.mask;
+                    if constexpr (PP) my_rpv[i] = pv[d];
+                }
+                rtail += (uint32_t)__popcll(m);
+                __builtin_amdgcn_wave_barrier();
+                if (rtail - rhead >= (uint32_t)kWave) retry(kWave);
+                __builtin_amdgcn_wave_barrier();
+            }
+        } else {
+            uint32_t off[D], word[D];
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                off[d] = (uint32_t)key[d] - (uint32_t)t.key_min;
+                if ((int64_t)off[d] >= t.span) ok &= ~(1u << d);
+                word[d] = t.bitmap[((ok >> d) & 1u) ? off[d] >> 5 : 0u];
+            }
+            int32_t pay[D];
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                if (!((word[d] >> (off[d] & 31u)) & 1u)) ok &= ~(1u << d);
+                pay[d] = t.has_payload && ((ok >> d) & 1u) ? t.payload[off[d]] : 0;
+            }
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                sum += (uint64_t)(int64_t)pay[d];
+                if constexpr (PP) sum += ((ok >> d) & 1u) ? (uint64_t)(int64_t)pv[d] : 0ull;
+            }
+            cnt += (uint64_t)__popc(ok);
+        }
+    };
+    auto run_tile = [&](int64_t tile, const ProbeRegs<IPT, PP> &r) {
+        const bool full = (tile + 1) * T::ITEMS <= n;
+        const uint32_t valid = valid_mask<BLOCK, IPT>(tile * T::ITEMS, n);
+#pragma unroll
+        for (int c = 0; c < IPT; c += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const int32_t k = r.key[c + d];
+                bool in = slice_of(k) == slice;
+                if (!full) in = in && ((valid >> (c + d)) & 1u);
+                const uint64_t m = ballot(in);
+                if (in) {
+                    const uint32_t i = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)m, tail)) & (kQ - 1u);
+                    my_key[i] = k;
+                    if constexpr (PP) my_pv[i] = r.pv[c + d];
+                }
+                tail += (uint32_t)__popcll(m);
+            }
+            __builtin_amdgcn_wave_barrier();
+            if (tail - head >= (uint32_t)(D * kWave)) drain(D * kWave);
+            __builtin_amdgcn_wave_barrier();
+        }
+    };
+    auto load = [&](int64_t tile, ProbeRegs<IPT, PP> &r) {
+        block_load<BLOCK, IPT, false>(fk, tile * T::ITEMS, n, r.key);
+        if constexpr (PP) block_load<BLOCK, IPT, false>(pp, tile * T::ITEMS, n, r.pv);
+    };
+    const int64_t stride = gridDim.x >> LG;
+    int64_t tile = blockIdx.x >> LG;
+    ProbeRegs<IPT, PP> ra, rb;
+    if (tile < n_tiles) load(tile, ra);
+    while (tile < n_tiles) {
+        if (tile + stride < n_tiles) load(tile + stride, rb);
+        run_tile(tile, ra);
+        tile += stride;
+        if (tile >= n_tiles) break;
+        if (tile + stride < n_tiles) load(tile + stride, ra);
+        run_tile(tile, rb);
+        tile += stride;
+    }
+    if (tail != head) drain(tail - head);
+    if (rtail != rhead) retry(rtail - rhead);
+    sum = wave_sum_u64(sum);
+    cnt = wave_sum_u64(cnt);
+    if (lane == 0) {
+        red[0][w] = sum;
+        red[1][w] = cnt;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        uint64_t x = 0;
+        for (int i = 0; i < T::WAVES; ++i) x += red[threadIdx.x][i];
+        if (x) atomic_add_u64(threadIdx.x ? out_cnt : out_sum, x);
+    }
+}
+
+template <int KIND, bool PP, int LG>
+static hipError_t sliced_launch(const DevTable &t, const int32_t *fk, const int32_t *pp, int64_t n, uint64_t *out,
+                                uint64_t *cnt, hipStream_t s) {
+    constexpr int B = 1024, I = PP ? 8 : 16;
+    const int64_t n_tiles = (n + (int64_t)B * I - 1) / ((int64_t)B * I);
+    auto fn = ht_probe_sliced_kernel<B, I, KIND, PP, LG>;
+    int64_t per_cu = 0;
+    hipError_t e = resident_per_cu((const void *)fn, B, 0, per_cu);
+    if (e != hipSuccess) return e;
+    int64_t per_slice = (per_cu < 1 ? 1 : per_cu) * device_cu_count() >> LG;
+    if (per_slice > n_tiles) per_slice = n_tiles;
+    if (per_slice < 1) per_slice = 1;
+    hipLaunchKernelGGL(fn, dim3((unsigned)(per_slice << LG)), dim3(B), 0, s, t, fk, pp, n, out, cnt, n_tiles);
+    return hipGetLastError();
+}
+
+template <int KIND>
+static hipError_t sliced_probe(int lg, const DevTable &t, const int32_t *fk, const int32_t *pp, int64_t n,
+                               uint64_t *out, uint64_t *cnt, hipStream_t s) {
+    if (pp) return sliced_launch<KIND, true, 2>(t, fk, pp, n, out, cnt, s);
+    return lg == 2 ? sliced_launch<KIND, false, 2>(t, fk, pp, n, out, cnt, s)
+                   : sliced_launch<KIND, false, 3>(t, fk, pp, n, out, cnt, s);
+}
+
+// log2 of the slices of a probe (0: not sliced).  `bytes` is what the probes
+// gather from: all slots, or a direct table's payloads (its bitmap is 32 times
+// smaller).  Up to 4 MB an XCD's L2 holds it; beyond, more slices fit L2 better
+// but each reads all keys, and payloads, again.  2^27 probes, in us, unsliced /
+// 4 slices / 8 slices:
+//   linear 8 MB 1,222/788/928, 16 MB 1,768/957/972, 32 MB 2,102/1,625/1,330,
+//   64 MB 2,409/2,214/2,005, 128 MB 2,505/2,976/2,883; with payloads 8 MB
+//   1,303/1,006/1,314, 16 MB 1,845/1,325/1,519, 32 MB 2,153/2,009/2,123, 64 MB
+//   2,461/2,514/2,746;
+//   direct 8 MB 1,399/1,059/1,086, 16 MB 1,865/1,342/1,269, 32 MB
+//   2,225/1,686/1,535; with payloads 8 MB 1,508/1,338/1,529, 16 MB
+//   1,943/1,568/1,733, 32 MB 2,303/2,031/2,205.
+// Short probes gain as well (2^18 into 16 MB: 35 -> 14 us).
+static int probe_slices_lg(const crystal_ht &ht, bool pp) {
+    const bool linear = ht.kind == CRYSTAL_HT_LINEAR;
+    const int64_t mb = int64_t(1) << 20;
+    const int64_t bytes = linear ? ht.capacity * 8 : ht.has_payload ? ht.capacity * 4 : 0;
+    if (bytes <= 4 * mb || bytes > (linear && !pp ? 64 : 32) * mb) return 0;
+    return pp || bytes <= (linear ? 16 : 8) * mb ? 2 : 3;
 }
 
 hipError_t launch_ht_probe(const LaunchCfg &cfg, const crystal_ht &ht, const int32_t *fk,
@@ -495,6 +782,11 @@ hipError_t launch_ht_probe(const LaunchCfg &cfg, const crystal_ht &ht, const int
                            hipStream_t s) {
     hipError_t e = zero_pair(sum, count, s);
     if (e != hipSuccess || n == 0) return e;
+    if (const int lg = probe_slices_lg(ht, probe_payload != nullptr)) {
+        const DevTable t = to_dev(ht);
+        return ht.kind == CRYSTAL_HT_LINEAR ? sliced_probe<CRYSTAL_HT_LINEAR>(lg, t, fk, probe_payload, n, sum, count, s)
+                                            : sliced_probe<CRYSTAL_HT_DIRECT>(lg, t, fk, probe_payload, n, sum, count, s);
+    }
     switch (CRYSTAL_VARIANT_KEY(cfg.block, cfg.ipt)) {
 #define X(B, I) \
     case CRYSTAL_VARIANT_KEY(B, I): return probe_t<B, I>(cfg, ht, fk, probe_payload, n, sum, count, s);

@@ -315,3 +315,35 @@ def test_build_batch_matches_single_builds():
             assert np.array_equal(occ_a[np.argsort(occ_a[:, 0])], occ_b[np.argsort(occ_b[:, 0])])
     with pytest.raises(cx.CrystalError):           # the same table twice
         cx.build_tables([items[0], items[0]])
+
+
+# ------------------------------------------- probes of large and staged tables --
+def _sliced_case(kind, dim, n, seed):
+    """Keys with a stride, so that homes collide and chains form; probe keys
+    that hit, miss inside and outside the key range, runs of one key (a whole
+    tile in one slice) and the empty key."""
+    rng = np.random.default_rng(seed)
+    step = 1 if kind == cx.HT_DIRECT else 4099
+    key = (rng.permutation(dim).astype(np.int64) * step - 5_000_000).astype(np.int32)
+    val = rng.integers(I32_MIN, I32_MAX, size=dim, dtype=np.int32, endpoint=True)
+    fk = key[rng.integers(0, dim, size=n)]
+    miss = rng.random(n) < 0.2
+    fk[miss] = rng.integers(I32_MIN, I32_MAX, size=int(miss.sum()), dtype=np.int32, endpoint=True)
+    fk[n // 3:n // 2] = key[0]
+    fk[n // 2:n // 2 + n // 50] = I32_MIN
+    return key, val, fk, rng.integers(I32_MIN, I32_MAX, size=n, dtype=np.int32, endpoint=True)
+
+
+@pytest.mark.parametrize("kind,dim", [
+    (cx.HT_LINEAR, (1 << 18) + 1), (cx.HT_LINEAR, 1 << 19), (cx.HT_LINEAR, (1 << 20) + 1),      # 4, 4 and 8 slices
+    (cx.HT_DIRECT, (1 << 20) + 1), (cx.HT_DIRECT, (1 << 21) + 7),                              # 4 and 8 slices
+    (cx.HT_DIRECT, 1), (cx.HT_DIRECT, 2049), (cx.HT_DIRECT, 38_000), (cx.HT_DIRECT, 40_001),   # all staged, bitmap staged
+    (cx.HT_DIRECT, 1 << 20)])
+@pytest.mark.parametrize("n", [1, 63, 16_385, 700_001])
+def test_probe_of_sliced_and_staged_tables(kind, dim, n):
+    announce("probe slices", kind, dim, n)
+    key, val, fk, pv = _sliced_case(kind, dim, n, dim + n)
+    ht = cx.HashTable(kind, dim, int(key.min()), int(key.max()))
+    cx.check_status(ht.build(dev(key), dev(val)))
+    assert tuple(ht.probe(dev(fk)).cpu().tolist()) == oracle.join_sum(key, val, fk)
+    assert tuple(ht.probe(dev(fk), dev(pv)).cpu().tolist()) == oracle.join_sum(key, val, fk, pval=pv)
