@@ -18,7 +18,7 @@
 // Two final launches sort every task in LDS by its remaining low bits
 // (stable 8-bit passes from the low digit up), one workgroup per task, and
 // write it to the output: tasks of at most kSmallMax pairs in a small shape
-// (four workgroups per CU), the others in a large one.  Levels alternate
+// (eight workgroups per CU), the others in a large one.  Levels alternate
 // between the output and a scratch copy; a task reads whichever holds its
 // segment.  Uniform keys need two partition levels (256, then
 // 65,536 segments of about 4,096 pairs) and the local pass; skewed keys
@@ -30,17 +30,17 @@
 
 #include "block.hpp"
 #include "internal.hpp"
+#include "radix_tile.hpp"
 
 namespace crystal {
 namespace {
 
-constexpr int kBinsM = 256;
 constexpr uint32_t kLocalMax = 8192;  // pairs one local-sort workgroup holds (512 threads x 16)
 constexpr uint32_t kSmallSeg = 1024;  // sub-segments shorter than this are grouped into one task
 constexpr uint32_t kChunk = 65536;    // pairs per partition chunk (4 tiles)
 constexpr int kPartBlock = 1024, kPartIpt = 16;
 constexpr int kLocBlock = 512, kLocIpt = 16;  // tasks up to kLocalMax pairs
-constexpr int kSmlBlock = 256, kSmlIpt = 17;  // tasks up to kSmallMax pairs, four workgroups per CU
+constexpr int kSmlBlock = 256, kSmlIpt = 17;  // tasks up to kSmallMax pairs, eight workgroups per CU
 constexpr uint32_t kSmallMax = kSmlBlock * kSmlIpt;
 static_assert(kLocBlock * kLocIpt >= (int)kLocalMax, "the large shape holds every sorted task");
 constexpr int kAuxBlock = 256;
@@ -90,29 +90,6 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t x, uint32_t *tmp, u
     total = tot;
     __syncthreads();
     return before + inc - x;
-}
-
-// Stable rank of item slot k among the wave's items of the same digit that
-// come before it (earlier slots through the wave's LDS counter wc[d], earlier
-// lanes of this slot through the ballots).  Invalid items are not counted.
-__device__ __forceinline__ uint32_t stable_rank(uint32_t d, bool valid, uint32_t *wc) {
-    uint64_t diff = 0;  // lanes whose digit differs from this lane's in some bit
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        const bool bit = (d >> b) & 1u;
-        const uint64_t m = ballot(bit);
-        diff |= bit ? ~m : m;
-    }
-    const uint64_t peers = ballot(valid) & ~diff;
-    const uint32_t below = count_below(peers);
-    const uint32_t same = (uint32_t)__popcll(peers);
-    uint32_t rank = 0;
-    if (valid) {
-        const uint32_t c = wc[d];
-        rank = c + below;
-        if (below + 1 == same) wc[d] = c + same;
-    }
-    return rank;
 }
 
 // ------------------------------------------------------------ work lists --
@@ -179,11 +156,11 @@ __global__ __launch_bounds__(kAuxBlock) void msb_hist_kernel(const Ctl *ctl, con
                                                              const uint32_t *__restrict__ keys, int shift,
                                                              uint32_t *__restrict__ hist) {
     constexpr int W = kAuxBlock / kWave;
-    __shared__ uint32_t h[W][kBinsM];
+    __shared__ uint32_t h[W][kBins];
     const int w = threadIdx.x / kWave;
     const uint32_t nc = ctl->n_chunks;
     for (uint32_t c = blockIdx.x; c < nc; c += gridDim.x) {
-        for (int i = threadIdx.x; i < W * kBinsM; i += kAuxBlock) (&h[0][0])[i] = 0u;
+        for (int i = threadIdx.x; i < W * kBins; i += kAuxBlock) (&h[0][0])[i] = 0u;
         __syncthreads();
         const ChunkD ch = chunks[c];
         // 16 keys per thread in flight at a time, then the tail
@@ -199,11 +176,11 @@ __global__ __launch_bounds__(kAuxBlock) void msb_hist_kernel(const Ctl *ctl, con
         for (i += threadIdx.x; i < ch.end; i += kAuxBlock)
             atomicAdd(&h[w][(__builtin_nontemporal_load(keys + i) >> shift) & 0xFFu], 1u);
         __syncthreads();
-        const int d = threadIdx.x;  // kAuxBlock == kBinsM
+        const int d = threadIdx.x;  // kAuxBlock == kBins
         uint32_t s = 0;
 #pragma unroll
         for (int i = 0; i < W; ++i) s += h[i][d];
-        hist[(int64_t)c * kBinsM + d] = s;
+        hist[(int64_t)c * kBins + d] = s;
         __syncthreads();
     }
 }
@@ -239,7 +216,7 @@ __device__ void plan_subsegments(Ctl *ctl, int cur, const uint32_t *st, const ui
                 g_len = 0;
                 g_digits = 0;
             };
-            for (int e = 0; e < kBinsM; ++e) {
+            for (int e = 0; e < kBins; ++e) {
                 const uint32_t len = tot[e];
                 if (!len) continue;
                 if (len > kLocalMax) {
@@ -270,7 +247,7 @@ __device__ void plan_subsegments(Ctl *ctl, int cur, const uint32_t *st, const ui
 // sub-segments.  One workgroup of 256 threads; also resets the counters.
 __global__ __launch_bounds__(kAuxBlock) void msb_level0_kernel(Ctl *ctl, const uint32_t *part, uint32_t n,
                                                                Seg *next, Task *tasks, uint32_t list_stride) {
-    __shared__ uint32_t st[kBinsM], tot[kBinsM];
+    __shared__ uint32_t st[kBins], tot[kBins];
     __shared__ uint32_t base_big, base_task[2];
     const int d = threadIdx.x;
     st[d] = part[d];
@@ -294,7 +271,7 @@ __global__ __launch_bounds__(kAuxBlock) void msb_scan_kernel(Ctl *ctl, const Seg
                                                              uint32_t *__restrict__ hist, Seg *next, Task *tasks,
                                                              uint32_t list_stride, int shift, uint32_t dst) {
     __shared__ uint32_t tmp[kAuxBlock / kWave];
-    __shared__ uint32_t st[kBinsM], tot[kBinsM];
+    __shared__ uint32_t st[kBins], tot[kBins];
     __shared__ uint32_t base_big, base_task[2];
     const int d = threadIdx.x;
     const uint32_t nb = ctl->n_big[cur];
@@ -302,7 +279,7 @@ __global__ __launch_bounds__(kAuxBlock) void msb_scan_kernel(Ctl *ctl, const Seg
         const Seg s = big[i];
         uint32_t run = 0;
         for (uint32_t j = 0; j < s.nchunks; ++j) {
-            uint32_t *p = hist + (int64_t)(s.chunk_base + j) * kBinsM + d;
+            uint32_t *p = hist + (int64_t)(s.chunk_base + j) * kBins + d;
             const uint32_t v = *p;
             *p = run;
             run += v;
@@ -310,7 +287,7 @@ __global__ __launch_bounds__(kAuxBlock) void msb_scan_kernel(Ctl *ctl, const Seg
         uint32_t unused;
         const uint32_t dstart = block_scan_excl<kAuxBlock>(run, tmp, unused);
         const uint32_t at = s.start + dstart;
-        for (uint32_t j = 0; j < s.nchunks; ++j) hist[(int64_t)(s.chunk_base + j) * kBinsM + d] += at;
+        for (uint32_t j = 0; j < s.nchunks; ++j) hist[(int64_t)(s.chunk_base + j) * kBins + d] += at;
         st[d] = at;
         tot[d] = run;
         __syncthreads();
@@ -322,132 +299,23 @@ __global__ __launch_bounds__(kAuxBlock) void msb_scan_kernel(Ctl *ctl, const Seg
 }
 
 // ---------------------------------------------------------------- shuffle --
-// Tile layout (as in the partition pass): wave w owns the 64 * IPT
-// consecutive pairs from w * 64 * IPT, and lane l's slot k is pair k * 64 + l
-// of them, so visiting slots in order visits a wave's pairs in input order.
 template <bool VALS>
-__global__ __launch_bounds__(kPartBlock) void msb_shuffle_kernel(const Ctl *ctl, const ChunkD *chunks,
-                                                                 const uint32_t *__restrict__ hist,
-                                                                 const uint32_t *__restrict__ ik,
-                                                                 const uint32_t *__restrict__ iv,
-                                                                 uint32_t *__restrict__ ok, uint32_t *__restrict__ ov,
-                                                                 int shift) {
-    constexpr int W = kPartBlock / kWave;
-    constexpr int ITEMS = kPartBlock * kPartIpt;
+__global__ __launch_bounds__(kPartBlock, 8) void msb_shuffle_kernel(const Ctl *ctl, const ChunkD *chunks,
+                                                                    const uint32_t *__restrict__ hist,
+                                                                    const uint32_t *__restrict__ ik,
+                                                                    const uint32_t *__restrict__ iv,
+                                                                    uint32_t *__restrict__ ok,
+                                                                    uint32_t *__restrict__ ov, int shift) {
+    using RT = RadixTile<kPartBlock, kPartIpt>;
     extern __shared__ uint32_t lds[];
-    uint32_t *s_keys = lds;
-    uint32_t *s_vals = lds + ITEMS;
-    uint32_t *s_wc = lds + (VALS ? 2 : 1) * ITEMS;  // [W][256]
-    uint32_t *s_gbase = s_wc + W * kBinsM;
-    uint32_t *s_run = s_gbase + kBinsM;
-    uint32_t *s_tmp = s_run + kBinsM;
-    const int tid = threadIdx.x;
-    const int w = tid / kWave;
-    uint32_t *my_wc = s_wc + w * kBinsM;
-    const int off0 = w * (kWave * kPartIpt) + (int)lane_id();
+    uint32_t *s_run = lds + RT::RUN;
     const uint32_t nc = ctl->n_chunks;
-
     for (uint32_t c = blockIdx.x; c < nc; c += gridDim.x) {
         const ChunkD ch = chunks[c];
-        if (tid < kBinsM) {
-            s_run[tid] = hist[(int64_t)c * kBinsM + tid];
-#pragma unroll
-            for (int i = 0; i < W; ++i) s_wc[i * kBinsM + tid] = 0u;
-        }
+        // the previous chunk last used s_run before its scatter barrier
+        if (threadIdx.x < kBins) s_run[threadIdx.x] = hist[(int64_t)c * kBins + threadIdx.x];
         __syncthreads();
-        uint32_t key[kPartIpt], val[kPartIpt];
-        auto load = [&](int64_t base) {
-            const int rem = (int)((int64_t)ch.end - base < ITEMS ? (int64_t)ch.end - base : ITEMS);
-            // the tile's base pointers are made opaque scalars, so every load
-            // is one scalar base plus one lane offset (global address space:
-            // a generic pointer would give flat loads)
-            typedef const __attribute__((address_space(1))) uint32_t *gptr;
-            // base is uniform; readfirstlane states it for the scalar constraint below
-            base = ((int64_t)__builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)base >> 32)) << 32) |
-                   (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)base);
-            gptr kb = (gptr)(ik + base);
-            gptr vb = VALS ? (gptr)(iv + base) : nullptr;
-            asm volatile("" : "+s"(kb));
-            if (VALS) asm volatile("" : "+s"(vb));
-            if (rem == ITEMS) {
-#pragma unroll
-                for (int k = 0; k < kPartIpt; ++k) {
-                    key[k] = __builtin_nontemporal_load(&kb[off0 + k * kWave]);
-                    if (VALS) val[k] = __builtin_nontemporal_load(&vb[off0 + k * kWave]);
-                }
-            } else {
-#pragma unroll
-                for (int k = 0; k < kPartIpt; ++k) {
-                    const int i = off0 + k * kWave;
-                    key[k] = i < rem ? kb[i] : 0u;
-                    if (VALS) val[k] = i < rem ? vb[i] : 0u;
-                }
-            }
-        };
-        load(ch.start);
-        for (int64_t base = ch.start; base < (int64_t)ch.end; base += ITEMS) {
-            const int rem = (int)((int64_t)ch.end - base < ITEMS ? (int64_t)ch.end - base : ITEMS);
-            // the wave clears its own counter row: the previous tile last read it
-            // in this wave and in the digit scan before its scatter barrier, so
-            // the write-out needs no barrier after it
-#pragma unroll
-            for (int q = 0; q < kBinsM / kWave; ++q) my_wc[q * kWave + (int)lane_id()] = 0u;
-            uint32_t rank[kPartIpt];
-#pragma unroll
-            for (int k = 0; k < kPartIpt; ++k) {
-                rank[k] = stable_rank((key[k] >> shift) & 0xFFu, off0 + k * kWave < rem, my_wc);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            __syncthreads();
-            // per digit: each wave's run inside the tile's run, the tile's
-            // digit starts, and the global base of the digit for this tile
-            uint32_t cnt = 0;
-            if (tid < kBinsM) {
-#pragma unroll
-                for (int i = 0; i < W; ++i) {
-                    const uint32_t v = s_wc[i * kBinsM + tid];
-                    s_wc[i * kBinsM + tid] = cnt;
-                    cnt += v;
-                }
-            }
-            uint32_t unused;
-            const uint32_t tstart = block_scan_excl<kPartBlock>(cnt, s_tmp, unused);
-            if (tid < kBinsM) {
-#pragma unroll
-                for (int i = 0; i < W; ++i) s_wc[i * kBinsM + tid] += tstart;
-                const uint32_t r = s_run[tid];
-                s_gbase[tid] = r - tstart;
-                s_run[tid] = r + cnt;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int k = 0; k < kPartIpt; ++k) {
-                if (off0 + k * kWave < rem) {
-                    const uint32_t p = my_wc[(key[k] >> shift) & 0xFFu] + rank[k];
-                    s_keys[p] = key[k];
-                    if (VALS) s_vals[p] = val[k];
-                }
-            }
-            __syncthreads();
-            // the next tile's loads go out while this one is written
-            if (base + ITEMS < (int64_t)ch.end) load(base + ITEMS);
-            int tidv = tid;  // opaque: keeps the write-out's per-item offsets out of registers
-            asm volatile("" : "+v"(tidv));
-#pragma unroll
-            for (int j = 0; j < kPartIpt; ++j) {
-                const int p = j * kPartBlock + tidv;
-                if (p < rem) {
-                    const uint32_t k = s_keys[p];
-                    const uint32_t g = s_gbase[(k >> shift) & 0xFFu] + (uint32_t)p;  // < n
-                    ok[g] = k;
-                    if (VALS) ov[g] = s_vals[p];
-                }
-                if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-            }
-            // no barrier: the next tile writes s_gbase, s_run, s_tmp and the LDS
-            // tile only after its ranking barrier, and the next chunk's set-up
-            // ends with one
-        }
+        shuffle_range<kPartBlock, kPartIpt, VALS, true>(ik, iv, ch.start, ch.end, shift, 0xFFu, ok, ov, lds);
     }
 }
 
@@ -455,47 +323,30 @@ __global__ __launch_bounds__(kPartBlock) void msb_shuffle_kernel(const Ctl *ctl,
 // One task at a time per workgroup: its pairs in registers (the tile layout
 // above), sorted by `bits` low key bits with stable 8-bit passes in LDS,
 // then written out from LDS.  Two shapes: BLOCK x IPT holds the task list's
-// largest task; the small shape fits four workgroups per CU.
+// largest task; the small shape fits eight workgroups per CU.
 template <bool VALS, int BLOCK, int IPT>
-__global__ __launch_bounds__(BLOCK, 4) void msb_local_kernel(const Ctl *ctl, int list, const Task *tasks,
-                                                          const uint32_t *__restrict__ in_k,
-                                                          const uint32_t *__restrict__ in_v,
-                                                          uint32_t *__restrict__ out_k, uint32_t *__restrict__ out_v,
-                                                          const uint32_t *__restrict__ tmp_k,
-                                                          const uint32_t *__restrict__ tmp_v) {
-    constexpr int W = BLOCK / kWave;
-    constexpr int ITEMS = BLOCK * IPT;
+__global__ __launch_bounds__(BLOCK, 8) void msb_local_kernel(const Ctl *ctl, int list, const Task *tasks,
+                                                             const uint32_t *__restrict__ in_k,
+                                                             const uint32_t *__restrict__ in_v,
+                                                             uint32_t *__restrict__ out_k,
+                                                             uint32_t *__restrict__ out_v,
+                                                             const uint32_t *__restrict__ tmp_k,
+                                                             const uint32_t *__restrict__ tmp_v) {
+    using RT = RadixTile<BLOCK, IPT>;
     extern __shared__ uint32_t lds[];
-    uint32_t *s_keys = lds;
-    uint32_t *s_vals = lds + ITEMS;
-    uint32_t *s_wc = lds + (VALS ? 2 : 1) * ITEMS;  // [W][256]
-    uint32_t *s_tmp = s_wc + W * kBinsM;
+    uint32_t *stage = lds + RT::STAGE;
+    uint16_t *wc = reinterpret_cast<uint16_t *>(lds + RT::WC);
     const int tid = threadIdx.x;
     const int w = tid / kWave;
-    uint32_t *my_wc = s_wc + w * kBinsM;
-    const int wave0 = w * (kWave * IPT);
-    const int off0 = wave0 + (int)lane_id();
+    uint16_t *my_wc = wc + w * kBins;
+    const int off0 = RT::offset(0);
     const uint32_t nt = ctl->n_tasks[list];
     auto src_k = [&](const Task &t) { return t.src == 0 ? in_k : t.src == 1 ? (const uint32_t *)out_k : tmp_k; };
     auto src_v = [&](const Task &t) { return t.src == 0 ? in_v : t.src == 1 ? (const uint32_t *)out_v : tmp_v; };
-    uint32_t key[IPT], val[IPT];
-    auto load = [&](const Task &t) {
-        typedef const __attribute__((address_space(1))) uint32_t *gptr;
-        gptr kb = (gptr)(src_k(t) + t.start);
-        gptr vb = VALS ? (gptr)(src_v(t) + t.start) : nullptr;
-        const int len = (int)t.len;
-#pragma unroll
-        for (int k = 0; k < IPT; ++k) {
-            const int i = off0 + k * kWave;
-            key[k] = i < len ? kb[i] : 0u;
-            if (VALS) val[k] = i < len ? vb[i] : 0u;
-        }
-    };
 
     for (uint32_t t = blockIdx.x; t < nt; t += gridDim.x) {
         const Task task = tasks[t];
         const int len = (int)task.len;
-        if (task.bits) load(task);
         if (task.bits == 0) {
             // already in order: copy unless it is in the output already
             if (task.src != 1) {
@@ -505,80 +356,54 @@ __global__ __launch_bounds__(BLOCK, 4) void msb_local_kernel(const Ctl *ctl, int
                     if (VALS) out_v[task.start + i] = sv[task.start + i];
                 }
             }
-        } else {
-            for (uint32_t sh = 0; sh < task.bits; sh += 8) {
-                const uint32_t left = task.bits - sh;
-                const uint32_t mask = left >= 8 ? 0xFFu : (1u << left) - 1u;
-                if (tid < kBinsM) {
-#pragma unroll
-                    for (int i = 0; i < W; ++i) s_wc[i * kBinsM + tid] = 0u;
-                }
-                __syncthreads();
-                uint32_t rank[IPT];
-                // slots whose 64 pairs all lie past the task's end are skipped
-                // (the test is uniform across the wave)
-#pragma unroll
-                for (int k = 0; k < IPT; ++k) {
-                    rank[k] = 0;
-                    if (wave0 + k * kWave < len)
-                        rank[k] = stable_rank((key[k] >> sh) & mask, off0 + k * kWave < len, my_wc);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                __syncthreads();
-                uint32_t cnt = 0;
-                if (tid < kBinsM) {
-#pragma unroll
-                    for (int i = 0; i < W; ++i) {
-                        const uint32_t v = s_wc[i * kBinsM + tid];
-                        s_wc[i * kBinsM + tid] = cnt;
-                        cnt += v;
-                    }
-                }
-                uint32_t unused;
-                const uint32_t dstart = block_scan_excl<BLOCK>(cnt, s_tmp, unused);
-                if (tid < kBinsM) {
-#pragma unroll
-                    for (int i = 0; i < W; ++i) s_wc[i * kBinsM + tid] += dstart;
-                }
-                __syncthreads();
-#pragma unroll
-                for (int k = 0; k < IPT; ++k) {
-                    if (off0 + k * kWave < len) {
-                        const uint32_t p = my_wc[(key[k] >> sh) & mask] + rank[k];
-                        s_keys[p] = key[k];
-                        if (VALS) s_vals[p] = val[k];
-                    }
-                }
-                __syncthreads();
-                if (sh + 8 < task.bits) {
-#pragma unroll
-                    for (int k = 0; k < IPT; ++k) {
-                        const int i = off0 + k * kWave;
-                        if (i < len) {
-                            key[k] = s_keys[i];
-                            if (VALS) val[k] = s_vals[i];
-                        }
-                    }
-                    __syncthreads();
-                }
-            }
+            continue;
         }
-        if (task.bits) {
-            for (int i = tid; i < len; i += BLOCK) {
-                out_k[task.start + i] = s_keys[i];
-                if (VALS) out_v[task.start + i] = s_vals[i];
+        uint32_t key[IPT], val[IPT];
+        load_tile<BLOCK, IPT, false>(src_k(task) + task.start, 0, len, off0, key);
+        if (VALS) load_tile<BLOCK, IPT, false>(src_v(task) + task.start, 0, len, off0, val);
+        for (uint32_t sh = 0; sh < task.bits; sh += 8) {
+            const uint32_t left = task.bits - sh;
+            const uint32_t mask = left >= 8 ? 0xFFu : (1u << left) - 1u;
+            Pos16<IPT> pos;
+            clear_counters(my_wc);
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int k = 0; k < IPT; ++k) {
+                pos.init(k, stable_rank(digit_of(key[k], (int)sh, mask), my_wc));
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __syncthreads();  // the LDS is the next task's
+            __syncthreads();
+            if (w == 0) {
+                uint32_t start[4], cnt[4];
+                scan_counters<RT::W>(wc, start, cnt);
+            }
+            __syncthreads();
+            place_keys<IPT>(key, (int)sh, mask, my_wc, pos, stage);
+            __syncthreads();
+            const bool last = sh + 8 >= task.bits;
+            if (last) {
+                for (int i = tid; i < len; i += BLOCK) out_k[task.start + i] = stage[i];
+            } else {
+#pragma unroll
+                for (int k = 0; k < IPT; ++k) key[k] = stage[off0 + k * kWave];
+            }
+            if constexpr (VALS) {
+                __syncthreads();
+#pragma unroll
+                for (int k = 0; k < IPT; ++k) stage[pos.get(k)] = val[k];
+                __syncthreads();
+                if (last) {
+                    for (int i = tid; i < len; i += BLOCK) out_v[task.start + i] = stage[i];
+                } else {
+#pragma unroll
+                    for (int k = 0; k < IPT; ++k) val[k] = stage[off0 + k * kWave];
+                }
+            }
+            // no barrier: the stage is written again only after the next
+            // ranking barrier, and a wave's counters were last read by the
+            // wave itself
         }
     }
-}
-
-constexpr size_t shuffle_lds(bool vals) {
-    return ((size_t)(vals ? 2 : 1) * kPartBlock * kPartIpt + (kPartBlock / kWave) * kBinsM + 2 * kBinsM +
-            kPartBlock / kWave) * 4;
-}
-constexpr size_t local_lds(bool vals, int block, int ipt) {
-    return ((size_t)(vals ? 2 : 1) * block * ipt + (block / kWave) * kBinsM + block / kWave) * 4;
 }
 
 int64_t r256(int64_t b) { return (b + 255) / 256 * 256; }
@@ -614,13 +439,13 @@ MsbLayout msb_layout(int64_t n, bool vals) {
     L.chunks = at;
     at += r256(L.max_chunks * (int64_t)sizeof(ChunkD));
     L.hist = at;
-    at += r256(L.max_chunks * kBinsM * 4);
+    at += r256(L.max_chunks * kBins * 4);
     L.tasks = at;  // two lists of max_tasks entries
     at += r256(2 * L.max_tasks * (int64_t)sizeof(Task));
     L.ctl = at;
     at += 256;
     L.part = at;
-    at += r256((kBinsM + 1) * 4);
+    at += r256((kBins + 1) * 4);
     L.pass = at;
     at += r256(radix_pass_scratch_bytes(tune_lookup(CRYSTAL_K_RADIX, n), n));
     L.total = at;
@@ -643,11 +468,12 @@ hipError_t msb_run(const uint32_t *keys, const uint32_t *vals, int64_t n, uint32
     const uint32_t stride = (uint32_t)L.max_tasks;
     auto large = msb_local_kernel<VALS, kLocBlock, kLocIpt>;
     auto small = msb_local_kernel<VALS, kSmlBlock, kSmlIpt>;
-    const size_t large_lds = local_lds(VALS, kLocBlock, kLocIpt), small_lds = local_lds(VALS, kSmlBlock, kSmlIpt);
+    const size_t large_lds = RadixTile<kLocBlock, kLocIpt>::BYTES, small_lds = RadixTile<kSmlBlock, kSmlIpt>::BYTES;
+    const size_t shuffle_lds = RadixTile<kPartBlock, kPartIpt>::BYTES;
     static bool attrs = false;
     if (!attrs) {
         hipError_t e = hipFuncSetAttribute((const void *)msb_shuffle_kernel<VALS>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)shuffle_lds(VALS));
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)shuffle_lds);
         if (e == hipSuccess)
             e = hipFuncSetAttribute((const void *)large, hipFuncAttributeMaxDynamicSharedMemorySize, (int)large_lds);
         if (e != hipSuccess) return e;
@@ -655,7 +481,7 @@ hipError_t msb_run(const uint32_t *keys, const uint32_t *vals, int64_t n, uint32
     }
     const int64_t cus = device_cu_count();
     int64_t part_per_cu = 0, large_per_cu = 0, small_per_cu = 0;
-    hipError_t e = resident_per_cu((const void *)msb_shuffle_kernel<VALS>, kPartBlock, (int64_t)shuffle_lds(VALS),
+    hipError_t e = resident_per_cu((const void *)msb_shuffle_kernel<VALS>, kPartBlock, (int64_t)shuffle_lds,
                                    part_per_cu);
     if (e == hipSuccess) e = resident_per_cu((const void *)large, kLocBlock, (int64_t)large_lds, large_per_cu);
     if (e == hipSuccess) e = resident_per_cu((const void *)small, kSmlBlock, (int64_t)small_lds, small_per_cu);
@@ -701,7 +527,7 @@ hipError_t msb_run(const uint32_t *keys, const uint32_t *vals, int64_t n, uint32
         hipLaunchKernelGGL(msb_scan_kernel, aux_grid, aux, 0, s, ctl, big[cur], cur, hist, big[cur ^ 1], tasks,
                            stride, shift, dst);
         hipLaunchKernelGGL(msb_shuffle_kernel<VALS>, dim3((unsigned)(cus * part_per_cu)), dim3(kPartBlock),
-                           shuffle_lds(VALS), s, ctl, chunks, hist, sk, sv, dk, dv, shift);
+                           shuffle_lds, s, ctl, chunks, hist, sk, sv, dk, dv, shift);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return local_sorts(cus * large_per_cu, cus * small_per_cu);

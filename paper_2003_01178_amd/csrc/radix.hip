@@ -27,37 +27,11 @@
 // Every load instruction of a wave reads 256 consecutive bytes.
 #include "block.hpp"
 #include "internal.hpp"
+#include "radix_tile.hpp"
 #include "variants.hpp"
 
 namespace crystal {
 namespace {
-
-constexpr int kBins = 256;  // digits of at most 8 bits
-
-template <int BLOCK, int IPT>
-struct RadixTile {
-    static_assert(BLOCK >= kBins, "one thread per digit");
-    static constexpr int W = BLOCK / kWave;
-    static constexpr int ITEMS = BLOCK * IPT;
-    __device__ static __forceinline__ int offset(int k) {
-        return (int)(threadIdx.x / kWave) * (kWave * IPT) + k * kWave + (int)(threadIdx.x % kWave);
-    }
-};
-
-__device__ __forceinline__ uint32_t digit_of(uint32_t key, int shift, uint32_t mask) {
-    return (key >> shift) & mask;
-}
-
-// Inclusive prefix over the 64 lanes of a wave.
-__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
-    const int lane = (int)lane_id();
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        uint32_t y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
-    return x;
-}
 
 // Exclusive prefix of x over threads 0 .. BLOCK-1 in thread order; `tmp` holds
 // one word per wave.  Every thread calls it.  With TRAIL it ends with a
@@ -195,54 +169,6 @@ __global__ __launch_bounds__(kScanBlock) void radix_scan_kernel(uint32_t *__rest
 }
 
 // --------------------------------------------------------------- shuffle --
-template <int BLOCK, int IPT, bool VALS>
-struct ShuffleLds {
-    static constexpr int W = BLOCK / kWave;
-    static constexpr int ITEMS = BLOCK * IPT;
-    // word offsets
-    static constexpr int KEYS = 0;
-    static constexpr int VALSO = KEYS + ITEMS;
-    static constexpr int WC = VALSO + (VALS ? ITEMS : 0);  // [W][kBins]
-    static constexpr int GBASE = WC + W * kBins;           // [kBins]
-    static constexpr int RUN = GBASE + kBins;              // [kBins]
-    static constexpr int TMP = RUN + kBins;                // [W]
-    static constexpr int WORDS = TMP + W;
-    static constexpr size_t BYTES = (size_t)WORDS * 4;
-};
-
-// The tile starting at `base`: slot k of this lane is item off0 + 64 k.  The
-// tile's base pointers are made opaque to the compiler so that it addresses
-// every item from one scalar base and one lane offset, instead of carrying a
-// 64-bit address per item from tile to tile.
-template <int BLOCK, int IPT, bool VALS>
-__device__ __forceinline__ void load_tile(const uint32_t *__restrict__ keys, const uint32_t *__restrict__ vals,
-                                          int64_t base, int rem, int off0, uint32_t (&key)[IPT],
-                                          uint32_t (&val)[IPT]) {
-    using RT = RadixTile<BLOCK, IPT>;
-    // base is uniform; readfirstlane states it, so that the scalar constraint
-    // below holds wherever the compiler places this call
-    base = ((int64_t)__builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)base >> 32)) << 32) |
-           (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)base);
-    const uint32_t *kb = keys + base;
-    const uint32_t *vb = VALS ? vals + base : nullptr;
-    asm volatile("" : "+s"(kb));
-    if (VALS) asm volatile("" : "+s"(vb));
-    if (rem >= RT::ITEMS) {
-#pragma unroll
-        for (int k = 0; k < IPT; ++k) {
-            key[k] = __builtin_nontemporal_load(kb + off0 + k * kWave);
-            if (VALS) val[k] = __builtin_nontemporal_load(vb + off0 + k * kWave);
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < IPT; ++k) {
-            const int i = off0 + k * kWave;
-            key[k] = i < rem ? kb[i] : 0u;
-            if (VALS) val[k] = i < rem ? vb[i] : 0u;
-        }
-    }
-}
-
 // One workgroup per chunk of tiles_per_block tiles (the chunks the count
 // matrix's columns b * sub .. b * sub + sub - 1 counted).  STABLE: ballot
 // ranking in input order; otherwise every item takes its rank from an LDS
@@ -250,143 +176,33 @@ __device__ __forceinline__ void load_tile(const uint32_t *__restrict__ keys, con
 // arbitrarily (the unstable shuffle of section 4.4) for far fewer
 // instructions per item.
 template <int BLOCK, int IPT, bool VALS, bool STABLE>
-__global__ __launch_bounds__(BLOCK) void radix_shuffle_kernel(
+__global__ __launch_bounds__(BLOCK, 8) void radix_shuffle_kernel(
     const uint32_t *__restrict__ keys, const uint32_t *__restrict__ vals, int64_t n, int shift, uint32_t mask,
     int64_t n_tiles, int64_t tiles_per_block, int sub, const uint32_t *__restrict__ counts, int64_t cols,
     const uint32_t *__restrict__ totals, uint32_t *__restrict__ out_keys, uint32_t *__restrict__ out_vals,
     uint32_t *__restrict__ part_offsets) {
     using RT = RadixTile<BLOCK, IPT>;
-    using L = ShuffleLds<BLOCK, IPT, VALS>;
     extern __shared__ uint32_t lds[];
-    uint32_t *s_keys = lds + L::KEYS;
-    uint32_t *s_vals = lds + L::VALSO;
-    uint32_t *s_wc = lds + L::WC;
-    uint32_t *s_gbase = lds + L::GBASE;
-    uint32_t *s_run = lds + L::RUN;
-    uint32_t *s_tmp = lds + L::TMP;
-
+    uint32_t *s_run = lds + RT::RUN;
     const int tid = threadIdx.x;
-    const int w = tid / kWave;
-    uint32_t *my_wc = s_wc + w * kBins;
 
-    // partition starts: exclusive prefix of the digit totals
+    // partition starts: exclusive prefix of the digit totals (the stage is free as scratch)
     uint32_t unused;
     const uint32_t tot = (tid < kBins && (uint32_t)tid <= mask) ? totals[tid] : 0u;
-    const uint32_t dstart = block_exclusive_scan_u32<BLOCK>(tot, s_tmp, unused);
+    const uint32_t dstart = block_exclusive_scan_u32<BLOCK>(tot, lds, unused);
     if (tid < kBins) {
-        if ((uint32_t)tid <= mask) {
-            s_run[tid] = dstart + counts[(int64_t)tid * cols + (int64_t)blockIdx.x * sub];
-            if (blockIdx.x == 0 && part_offsets) part_offsets[tid] = dstart;
-        }
+        s_run[tid] = (uint32_t)tid <= mask ? dstart + counts[(int64_t)tid * cols + (int64_t)blockIdx.x * sub] : 0u;
+        if (blockIdx.x == 0 && part_offsets && (uint32_t)tid <= mask) part_offsets[tid] = dstart;
     }
     if (blockIdx.x == 0 && part_offsets && tid == 0) part_offsets[mask + 1] = (uint32_t)n;
     __syncthreads();
 
-    int64_t t0 = (int64_t)blockIdx.x * tiles_per_block;
+    const int64_t t0 = (int64_t)blockIdx.x * tiles_per_block;
     int64_t t1 = t0 + tiles_per_block;
     if (t1 > n_tiles) t1 = n_tiles;
     if (t0 >= t1) return;
-
-    // slot k of this lane sits at tile offset off0 + 64 k
-    const int off0 = RT::offset(0);
-    auto items_from = [&](int64_t b) { return n - b >= RT::ITEMS ? RT::ITEMS : (int)(n - b); };
-    uint32_t key[IPT], val[IPT];
-    load_tile<BLOCK, IPT, VALS>(keys, vals, t0 * RT::ITEMS, items_from(t0 * RT::ITEMS), off0, key, val);
-    for (int64_t t = t0; t < t1; ++t) {
-        const int64_t base = t * RT::ITEMS;
-        const int rem = items_from(base);  // items in this tile
-        int tidv = tid;                    // opaque: keeps per-item offsets out of registers
-        asm volatile("" : "+v"(tidv));
-        // 1. rank every item among the wave's earlier items of its digit.  The
-        //    wave clears its own counter row first: the previous tile last read
-        //    it in this wave (step 3) and in the digit scan before that tile's
-        //    scatter barrier, so no barrier is needed after the write-out, and a
-        //    wave done writing ranks the next tile while others still write.
-#pragma unroll
-        for (int q = 0; q < kBins / kWave; ++q) my_wc[q * kWave + (int)lane_id()] = 0u;
-        uint32_t rank[IPT];
-        if constexpr (!STABLE) {
-#pragma unroll
-            for (int k = 0; k < IPT; ++k) {
-                rank[k] = 0;
-                if (off0 + k * kWave < rem) rank[k] = atomicAdd(&my_wc[digit_of(key[k], shift, mask)], 1u);
-            }
-        } else
-#pragma unroll
-        for (int k = 0; k < IPT; ++k) {
-            const bool valid = off0 + k * kWave < rem;
-            const uint32_t d = digit_of(key[k], shift, mask);
-            // lanes whose digit differs from this lane's in some bit
-            uint64_t diff = 0;
-#pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const bool bit = (d >> b) & 1u;
-                const uint64_t m = ballot(bit);
-                diff |= bit ? ~m : m;
-            }
-            const uint64_t peers = ballot(valid) & ~diff;
-            const uint32_t below = count_below(peers);
-            const uint32_t same = (uint32_t)__popcll(peers);
-            rank[k] = 0;
-            if (valid) {
-                const uint32_t c = my_wc[d];
-                rank[k] = c + below;
-                if (below + 1 == same) my_wc[d] = c + same;
-            }
-            // one slot at a time: interleaving slots only raises register pressure,
-            // since each slot waits for the previous slot's counter update anyway
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        __syncthreads();
-        // 2. per digit: offsets of each wave's run inside the tile's run of
-        //    that digit, the tile's digit starts, and the global base
-        uint32_t cnt = 0;
-        if (tid < kBins) {
-#pragma unroll
-            for (int i = 0; i < RT::W; ++i) {
-                const uint32_t c = s_wc[i * kBins + tid];
-                s_wc[i * kBins + tid] = cnt;
-                cnt += c;
-            }
-        }
-        // no trailing barrier: s_tmp is next written after this tile's later barriers
-        const uint32_t tstart = block_exclusive_scan_u32<BLOCK, false>(cnt, s_tmp, unused);
-        if (tid < kBins) {
-#pragma unroll
-            for (int i = 0; i < RT::W; ++i) s_wc[i * kBins + tid] += tstart;
-            const uint32_t run = s_run[tid];
-            s_gbase[tid] = run - tstart;
-            s_run[tid] = run + cnt;
-        }
-        __syncthreads();
-        // 3. the tile, sorted by digit (stable), into LDS
-#pragma unroll
-        for (int k = 0; k < IPT; ++k) {
-            if (off0 + k * kWave < rem) {
-                const uint32_t p = my_wc[digit_of(key[k], shift, mask)] + rank[k];
-                s_keys[p] = key[k];
-                if (VALS) s_vals[p] = val[k];
-            }
-        }
-        __syncthreads();
-        // 4. next tile's loads go out while this one is written
-        if (t + 1 < t1)
-            load_tile<BLOCK, IPT, VALS>(keys, vals, base + RT::ITEMS, items_from(base + RT::ITEMS), off0, key, val);
-#pragma unroll
-        for (int j = 0; j < IPT; ++j) {
-            const int p = j * BLOCK + tidv;
-            if (p < rem) {
-                const uint32_t k = s_keys[p];
-                const uint32_t g = s_gbase[digit_of(k, shift, mask)] + (uint32_t)p;  // < n < 2^32
-                out_keys[g] = k;
-                if (VALS) out_vals[g] = s_vals[p];
-            }
-            if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-        // no barrier: the next tile writes s_gbase, s_run, s_tmp and the LDS
-        // tile only after its ranking barrier, which every wave reaches after
-        // finishing this write-out
-    }
+    const int64_t end = t1 * RT::ITEMS < n ? t1 * RT::ITEMS : n;
+    shuffle_range<BLOCK, IPT, VALS, STABLE>(keys, vals, t0 * RT::ITEMS, end, shift, mask, out_keys, out_vals, lds);
 }
 
 // ---------------------------------------------------------------- launch --
@@ -403,7 +219,7 @@ struct RadixKernels {
         if (done) return hipSuccess;
         hipError_t e = hipFuncSetAttribute((const void *)radix_shuffle_kernel<BLOCK, IPT, VALS, STABLE>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)ShuffleLds<BLOCK, IPT, VALS>::BYTES);
+                                           (int)RadixTile<BLOCK, IPT>::BYTES);
         if (e == hipSuccess) done = true;
         return e;
     }
@@ -427,7 +243,7 @@ struct RadixKernels {
                                 uint32_t *ov, uint32_t *part_offsets, hipStream_t s) {
         hipError_t e = prepare_one<VALS, STABLE>();
         if (e != hipSuccess) return e;
-        const size_t lds = ShuffleLds<BLOCK, IPT, VALS>::BYTES;
+        const size_t lds = RadixTile<BLOCK, IPT>::BYTES;
         hipLaunchKernelGGL((radix_shuffle_kernel<BLOCK, IPT, VALS, STABLE>), dim3((unsigned)g.grid), dim3(BLOCK),
                            lds, s, keys, vals, n, shift, mask, g.n_tiles, g.tiles_per_block, g.sub, counts, g.cols,
                            totals, ok, ov, part_offsets);
@@ -449,7 +265,7 @@ struct RadixKernels {
 size_t shuffle_lds_bytes(int block, int ipt) {
     switch (CRYSTAL_VARIANT_KEY(block, ipt)) {
 #define X(B, I) \
-    case CRYSTAL_VARIANT_KEY(B, I): return ShuffleLds<B, I, true>::BYTES;
+    case CRYSTAL_VARIANT_KEY(B, I): return RadixTile<B, I>::BYTES;
         CRYSTAL_VARIANTS_RADIX(X)
 #undef X
     default: return 0;
