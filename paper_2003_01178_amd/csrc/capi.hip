@@ -86,7 +86,9 @@ struct TuneEntry {
 static std::mutex g_tune_mu;
 static std::vector<TuneEntry> g_tune;
 
-static LaunchCfg default_cfg(int kernel) {
+static constexpr LaunchCfg kRadixLong = {1024, 16, 0};
+
+static LaunchCfg default_cfg(int kernel, int64_t n) {
     switch (kernel) {
     case CRYSTAL_K_SELECT: return {1024, 16, 0};
     case CRYSTAL_K_PROJECT: return {256, 16, 0};
@@ -95,7 +97,16 @@ static LaunchCfg default_cfg(int kernel) {
     case CRYSTAL_K_STAR: return {256, 16, 0};
     case CRYSTAL_K_SHARED_SCAN: return {1024, 16, 0};
     case CRYSTAL_K_SHARED_SCAN_SCALAR: return {1024, 8, 0};
-    case CRYSTAL_K_RADIX: return {1024, 16, 0};
+    case CRYSTAL_K_RADIX:
+        // Short inputs: small tiles, so that more CUs share them; the sort's
+        // four passes, pairs, in us, at this shape and at 1024 x 16: 30,000
+        // 37/90, 100,003 45/82, 400,000 53/91, 1M 62/91, 2M 79/99, 10M 231/207
+        // (512 x 8 / 1024 x 16 from 2M on).  Long ones: the longest runs.
+        if (n <= 1 << 16) return {256, 4, 0};
+        if (n <= 1 << 18) return {512, 4, 0};
+        if (n <= 1 << 20) return {1024, 4, 0};
+        if (n <= 1 << 23) return {512, 8, 0};
+        return kRadixLong;
     default: return {256, 16, 0};
     }
 }
@@ -106,12 +117,39 @@ static int size_bucket(int64_t n) {
     return b;
 }
 
-LaunchCfg tune_lookup(int kernel, int64_t n) {
+static bool tuned(int kernel, int64_t n, LaunchCfg &cfg) {
     const int b = size_bucket(n);
     std::lock_guard<std::mutex> lk(g_tune_mu);
     for (auto it = g_tune.rbegin(); it != g_tune.rend(); ++it)
-        if (it->kernel == kernel && b >= it->blo && b <= it->bhi) return it->cfg;
-    return default_cfg(kernel);
+        if (it->kernel == kernel && b >= it->blo && b <= it->bhi) {
+            cfg = it->cfg;
+            return true;
+        }
+    return false;
+}
+
+LaunchCfg tune_lookup(int kernel, int64_t n) {
+    LaunchCfg c;
+    return tuned(kernel, n, c) ? c : default_cfg(kernel, n);
+}
+
+LaunchCfg radix_long_cfg(int64_t n) {
+    LaunchCfg c;
+    return tuned(CRYSTAL_K_RADIX, n, c) ? c : kRadixLong;
+}
+
+// Scratch of a partition pass: what is asked for, and the least accepted.
+static int64_t radix_scratch_least(int64_t n) { return radix_pass_min_scratch_bytes(radix_long_cfg(n), n); }
+static int64_t radix_scratch_bytes(int64_t n) {
+    const int64_t best = radix_pass_scratch_bytes(tune_lookup(CRYSTAL_K_RADIX, n), n), least = radix_scratch_least(n);
+    return best > least ? best : least;
+}
+
+// Shape of a partition pass with so much scratch: smaller tiles need more of
+// it, and a call that brings only the least runs with the long shape.
+static LaunchCfg radix_cfg(int64_t n, int64_t scratch_bytes) {
+    const LaunchCfg c = tune_lookup(CRYSTAL_K_RADIX, n);
+    return scratch_bytes < radix_pass_scratch_bytes(c, n) ? radix_long_cfg(n) : c;
 }
 
 static bool variant_exists(int kernel, int block, int ipt) {
@@ -666,7 +704,7 @@ crystal_status crystal_radix_histogram(const uint32_t *keys, int64_t n, int32_t 
 }
 
 size_t crystal_radix_partition_scratch_bytes(int64_t n) {
-    return (size_t)radix_pass_scratch_bytes(tune_lookup(CRYSTAL_K_RADIX, n), n);
+    return (size_t)radix_scratch_bytes(n);
 }
 
 static crystal_status radix_partition_common(const uint32_t *keys, const uint32_t *vals, int64_t n, int32_t shift,
@@ -675,14 +713,14 @@ static crystal_status radix_partition_common(const uint32_t *keys, const uint32_
                                              void *stream, bool stable) {
     if (bits < 1 || bits > 8 || shift < 0 || shift + bits > 32 || !radix_args_ok(keys, vals, n, out_keys, out_vals))
         return CRYSTAL_EINVAL;
-    const LaunchCfg cfg = tune_lookup(CRYSTAL_K_RADIX, n);
+    const LaunchCfg cfg = radix_cfg(n, (int64_t)scratch_bytes);
     if (!radix_variant_fits(cfg.block, cfg.ipt)) return CRYSTAL_EINVAL;
     if (n > 0) {
         if (!scratch || ((uintptr_t)scratch & 255u)) return scratch ? CRYSTAL_EINVAL : CRYSTAL_ESCRATCH;
-        if (scratch_bytes < (size_t)radix_pass_scratch_bytes(cfg, n)) return CRYSTAL_ESCRATCH;
+        if (scratch_bytes < (size_t)radix_scratch_least(n)) return CRYSTAL_ESCRATCH;
     }
     return from_hip(launch_radix_partition(cfg, keys, vals, n, shift, bits, out_keys, out_vals, part_offsets,
-                                           scratch, stable, as_stream(stream)));
+                                           scratch, (int64_t)scratch_bytes, stable, as_stream(stream)));
 }
 
 crystal_status crystal_radix_partition(const uint32_t *keys, const uint32_t *vals, int64_t n, int32_t shift,
@@ -706,33 +744,42 @@ static int64_t round256(int64_t b) { return (b + 255) / 256 * 256; }
 size_t crystal_sort_pairs_scratch_bytes(int64_t n, int32_t with_values) {
     if (n <= 0) return 256;
     const int64_t copy = round256(n * 4);
-    return (size_t)(copy * (with_values ? 2 : 1) +
-                    radix_pass_scratch_bytes(tune_lookup(CRYSTAL_K_RADIX, n), n));
+    return (size_t)(copy * (with_values ? 2 : 1) + radix_scratch_bytes(n));
+}
+
+// Four stable 8-bit passes from the low byte up, in -> tmp -> out -> tmp ->
+// out; `pass`: scratch of one pass.
+static crystal_status sort_lsb(const LaunchCfg &cfg, const uint32_t *keys, const uint32_t *vals, int64_t n,
+                               uint32_t *out_keys, uint32_t *out_vals, uint32_t *tk, uint32_t *tv, void *pass,
+                               int64_t pass_bytes, void *stream) {
+    const uint32_t *ik[4] = {keys, tk, out_keys, tk};
+    const uint32_t *iv[4] = {vals, tv, out_vals, tv};
+    uint32_t *ok[4] = {tk, out_keys, tk, out_keys};
+    uint32_t *ov[4] = {tv, out_vals, tv, out_vals};
+    for (int p = 0; p < 4; ++p) {
+        hipError_t e = launch_radix_partition(cfg, ik[p], iv[p], n, 8 * p, 8, ok[p], ov[p], nullptr, pass, pass_bytes,
+                                              true, as_stream(stream));
+        if (e != hipSuccess) return CRYSTAL_EHIP;
+    }
+    return CRYSTAL_OK;
 }
 
 crystal_status crystal_sort_pairs(const uint32_t *keys, const uint32_t *vals, int64_t n, uint32_t *out_keys,
                                   uint32_t *out_vals, void *scratch, size_t scratch_bytes, void *stream) {
     if (!radix_args_ok(keys, vals, n, out_keys, out_vals)) return CRYSTAL_EINVAL;
     if (n == 0) return CRYSTAL_OK;
-    const LaunchCfg cfg = tune_lookup(CRYSTAL_K_RADIX, n);
+    const int64_t copy = round256(n * 4);
+    const int64_t pass_bytes = (int64_t)scratch_bytes - copy * (vals ? 2 : 1);
+    const LaunchCfg cfg = radix_cfg(n, pass_bytes);
     if (!radix_variant_fits(cfg.block, cfg.ipt)) return CRYSTAL_EINVAL;
     if (!scratch || ((uintptr_t)scratch & 255u)) return scratch ? CRYSTAL_EINVAL : CRYSTAL_ESCRATCH;
-    if (scratch_bytes < crystal_sort_pairs_scratch_bytes(n, vals != nullptr)) return CRYSTAL_ESCRATCH;
-    const int64_t copy = round256(n * 4);
+    if (pass_bytes < radix_scratch_least(n)) return CRYSTAL_ESCRATCH;
+    // one workgroup, one launch: 8,192 pairs 76 -> 22 us, 1,000 66 -> 11 us
+    if (n <= kSortShortMax) return from_hip(launch_sort_short(keys, vals, n, out_keys, out_vals, as_stream(stream)));
     uint32_t *tk = (uint32_t *)scratch;
     uint32_t *tv = vals ? (uint32_t *)((char *)scratch + copy) : nullptr;
-    void *pass = (char *)scratch + copy * (vals ? 2 : 1);
-    // in -> tmp -> out -> tmp -> out, 8 bits per pass from the low byte up
-    const uint32_t *ik[4] = {keys, tk, out_keys, tk};
-    const uint32_t *iv[4] = {vals, tv, out_vals, tv};
-    uint32_t *ok[4] = {tk, out_keys, tk, out_keys};
-    uint32_t *ov[4] = {tv, out_vals, tv, out_vals};
-    for (int p = 0; p < 4; ++p) {
-        hipError_t e = launch_radix_partition(cfg, ik[p], iv[p], n, 8 * p, 8, ok[p], ov[p], nullptr, pass, true,
-                                              as_stream(stream));
-        if (e != hipSuccess) return CRYSTAL_EHIP;
-    }
-    return CRYSTAL_OK;
+    return sort_lsb(cfg, keys, vals, n, out_keys, out_vals, tk, tv, (char *)scratch + copy * (vals ? 2 : 1),
+                    pass_bytes, stream);
 }
 
 size_t crystal_sort_pairs_msb_scratch_bytes(int64_t n, int32_t with_values) {
@@ -746,8 +793,23 @@ crystal_status crystal_sort_pairs_msb(const uint32_t *keys, const uint32_t *vals
     if (n == 0) return CRYSTAL_OK;
     if (!scratch || ((uintptr_t)scratch & 255u)) return scratch ? CRYSTAL_EINVAL : CRYSTAL_ESCRATCH;
     if (scratch_bytes < crystal_sort_pairs_msb_scratch_bytes(n, vals != nullptr)) return CRYSTAL_ESCRATCH;
-    const LaunchCfg cfg = tune_lookup(CRYSTAL_K_RADIX, n);  // the first level's partition pass
+    const LaunchCfg cfg = radix_long_cfg(n);  // the first level's partition pass
     if (!radix_variant_fits(cfg.block, cfg.ipt)) return CRYSTAL_EINVAL;
+    if (n <= kSortShortMax) return from_hip(launch_sort_short(keys, vals, n, out_keys, out_vals, as_stream(stream)));
+    // Below 2^25 pairs four passes from the low byte up, which give the same
+    // order, are faster than the levels, and do not depend on the keys (pairs,
+    // in us, passes / levels: 100,003 45/172, 1M 63/84, 10M 217/280, 33M
+    // 565/647, 60M 1,116/1,078; 20-bit keys 33M 634/924).  A tuned shape keeps
+    // the levels.
+    LaunchCfg set;
+    if (n <= int64_t(1) << 25 && !tuned(CRYSTAL_K_RADIX, n, set)) {
+        const int64_t copy = round256(n * 4);
+        const int64_t pass_bytes = (int64_t)scratch_bytes - copy * (vals ? 2 : 1);
+        uint32_t *tk = (uint32_t *)scratch;
+        uint32_t *tv = vals ? (uint32_t *)((char *)scratch + copy) : nullptr;
+        return sort_lsb(radix_cfg(n, pass_bytes), keys, vals, n, out_keys, out_vals, tk, tv,
+                        (char *)scratch + copy * (vals ? 2 : 1), pass_bytes, stream);
+    }
     return from_hip(launch_msb_sort(keys, vals, n, out_keys, out_vals, scratch, as_stream(stream)));
 }
 

@@ -35,6 +35,8 @@ inline int64_t grid_for(int64_t n_tiles, const LaunchCfg &cfg) {
 }
 
 LaunchCfg tune_lookup(int kernel, int64_t n);
+// Radix shape for a partition of many tiles per CU: the tuned one, else 1024 x 16.
+LaunchCfg radix_long_cfg(int64_t n);
 
 inline crystal_status from_hip(hipError_t e) {
     return e == hipSuccess ? CRYSTAL_OK : CRYSTAL_EHIP;
@@ -84,6 +86,10 @@ hipError_t launch_ht_build_batch(const crystal_ht_build_item *items, int n_items
                                  hipStream_t s);
 // MSB radix sort of key/value pairs (vals, out_vals may be null together).
 int64_t msb_sort_scratch_bytes(int64_t n, bool with_values);
+// Stable sort of at most kSortShortMax pairs in one workgroup, without scratch.
+constexpr int64_t kSortShortMax = 8192;
+hipError_t launch_sort_short(const uint32_t *keys, const uint32_t *vals, int64_t n, uint32_t *out_keys,
+                             uint32_t *out_vals, hipStream_t s);
 hipError_t launch_msb_sort(const uint32_t *keys, const uint32_t *vals, int64_t n, uint32_t *out_keys,
                            uint32_t *out_vals, void *scratch, hipStream_t s);
 
@@ -235,7 +241,10 @@ hipError_t launch_star(const LaunchCfg &cfg, const StarPlanDev &plan, uint64_t *
                        int32_t *status, uint64_t *partials, bool accumulate, hipStream_t s);
 
 // ----------------------------------------------------------------- radix --
-// Scratch of one partition pass (count matrix + digit totals) under cfg.
+// Scratch of one partition pass (counts and digit totals) under cfg: the least
+// a pass of several tiles per workgroup runs with, and what one of a tile per
+// workgroup takes.
+int64_t radix_pass_min_scratch_bytes(const LaunchCfg &cfg, int64_t n);
 int64_t radix_pass_scratch_bytes(const LaunchCfg &cfg, int64_t n);
 // Whether the (block, ipt) shuffle variant exists and its LDS fits a workgroup.
 bool radix_variant_fits(int block, int ipt);
@@ -243,6 +252,7 @@ hipError_t launch_radix_histogram(const LaunchCfg &cfg, const uint32_t *keys, in
                                   uint32_t *hist, hipStream_t s);
 hipError_t launch_radix_partition(const LaunchCfg &cfg, const uint32_t *keys, const uint32_t *vals, int64_t n,
                                   int shift, int bits, uint32_t *out_keys, uint32_t *out_vals,
-                                  uint32_t *part_offsets, void *scratch, bool stable, hipStream_t s);
+                                  uint32_t *part_offsets, void *scratch, int64_t scratch_bytes, bool stable,
+                                  hipStream_t s);
 
 }  // namespace crystal

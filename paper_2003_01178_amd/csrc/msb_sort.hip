@@ -6,7 +6,7 @@
 // input is one segment).  Level L >= 1 (shift 24 - 8L) partitions every
 // "big" segment (more pairs than a workgroup sorts in LDS) by its digit at
 // `shift`, stably:
-//   chunks    each big segment is cut into chunks of at most kChunk pairs;
+//   chunks    each big segment is cut into chunks of one tile;
 //   histogram one workgroup counts the digits of a chunk;
 //   scan      one workgroup per segment turns its chunks' counts into output
 //             offsets (digit-major within the segment) and classifies the
@@ -37,8 +37,9 @@ namespace {
 
 constexpr uint32_t kLocalMax = 8192;  // pairs one local-sort workgroup holds (512 threads x 16)
 constexpr uint32_t kSmallSeg = 1024;  // sub-segments shorter than this are grouped into one task
-constexpr uint32_t kChunk = 65536;    // pairs per partition chunk (4 tiles)
 constexpr int kPartBlock = 1024, kPartIpt = 16;
+constexpr uint32_t kChunk = kPartBlock * kPartIpt;  // pairs per partition chunk: one tile
+constexpr uint32_t kCopy = 65536;     // pairs per copy task
 constexpr int kLocBlock = 512, kLocIpt = 16;  // tasks up to kLocalMax pairs
 constexpr int kSmlBlock = 256, kSmlIpt = 17;  // tasks up to kSmallMax pairs, eight workgroups per CU
 constexpr uint32_t kSmallMax = kSmlBlock * kSmlIpt;
@@ -61,6 +62,7 @@ struct Ctl {
     uint32_t n_big[2];
     uint32_t n_chunks;
     uint32_t n_tasks[2];
+    uint32_t taken[8];  // chunks of each XCD's range taken beyond its workgroups' first
 };
 
 __device__ __forceinline__ int task_list(uint32_t len, uint32_t bits) { return bits && len <= kSmallMax ? 0 : 1; }
@@ -93,17 +95,6 @@ __device__ __forceinline__ uint32_t block_scan_excl(uint32_t x, uint32_t *tmp, u
 }
 
 // ------------------------------------------------------------ work lists --
-// An input of at most kLocalMax pairs: one task, the whole input, all 32 bits.
-__global__ void msb_init_kernel(Ctl *ctl, Task *tasks, uint32_t list_stride, uint32_t n) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    ctl->n_big[0] = ctl->n_big[1] = 0;
-    ctl->n_chunks = 0;
-    const int l = task_list(n, 32u);
-    ctl->n_tasks[0] = ctl->n_tasks[1] = 0;
-    ctl->n_tasks[l] = 1;
-    tasks[(int64_t)l * list_stride] = Task{0u, n, 32u, 0u};
-}
-
 // One workgroup: chunk counts of the level's big segments, their exclusive
 // prefix (each segment's first chunk), the level's chunk total; clears the
 // next level's big-segment count.
@@ -128,6 +119,7 @@ __global__ __launch_bounds__(1024) void msb_chunk_scan_kernel(Ctl *ctl, Seg *big
         ctl->n_chunks = total;
         ctl->n_big[cur ^ 1] = 0;
     }
+    if (threadIdx.x < 8) ctl->taken[threadIdx.x] = 0;
 }
 
 // Chunk c of the level: its segment (binary search over the segments' first
@@ -191,7 +183,7 @@ __global__ __launch_bounds__(kAuxBlock) void msb_hist_kernel(const Ctl *ctl, con
 // more are tasks of their own, sorted by the `shift` bits below their digit;
 // shorter neighbours are grouped into tasks of at most kLocalMax pairs,
 // sorted by their digit too.  At the last digit every sub-segment is final
-// where the level wrote it: copy tasks of at most kChunk pairs when that is
+// where the level wrote it: copy tasks of at most kCopy pairs when that is
 // the scratch copy.  Two walks: count and reserve, then write.
 __device__ void plan_subsegments(Ctl *ctl, int cur, const uint32_t *st, const uint32_t *tot, uint32_t seg_start,
                                  uint32_t seg_len, int shift, uint32_t dst, Seg *next, Task *tasks,
@@ -204,11 +196,11 @@ __device__ void plan_subsegments(Ctl *ctl, int cur, const uint32_t *st, const ui
             ++ntask[l];
         };
         if (shift == 0) {
-            // copies in pieces of kChunk pairs, so that a long run of one key
+            // copies in pieces of kCopy pairs, so that a long run of one key
             // is copied by many workgroups
             if (dst != 1u)
-                for (uint64_t a = 0; a < seg_len; a += kChunk)
-                    emit_task(seg_start + (uint32_t)a, seg_len - a < kChunk ? (uint32_t)(seg_len - a) : kChunk, 0u);
+                for (uint64_t a = 0; a < seg_len; a += kCopy)
+                    emit_task(seg_start + (uint32_t)a, seg_len - a < kCopy ? (uint32_t)(seg_len - a) : kCopy, 0u);
         } else {
             uint32_t g_start = 0, g_len = 0, g_digits = 0;
             auto flush = [&]() {
@@ -242,6 +234,44 @@ __device__ void plan_subsegments(Ctl *ctl, int cur, const uint32_t *st, const ui
     }
 }
 
+// The same by the whole workgroup, thread d for digit d; called by all with
+// st and tot written, ends with a barrier.  One thread's two walks over the
+// digits took 60 us; when no sub-segment is short enough to be grouped (the
+// usual case of a long segment), each thread emits its own.
+__device__ __forceinline__ void plan_segment(Ctl *ctl, int cur, const uint32_t *st, const uint32_t *tot,
+                                             uint32_t seg_start, uint32_t seg_len, int shift, uint32_t dst, Seg *next,
+                                             Task *tasks, uint32_t list_stride, uint32_t &base_big,
+                                             uint32_t *base_task) {
+    const int d = (int)threadIdx.x;
+    __syncthreads();
+    const uint32_t len = tot[d];
+    if (__syncthreads_or(shift == 0 || (len > 0 && len < kSmallSeg))) {
+        if (d == 0)
+            plan_subsegments(ctl, cur, st, tot, seg_start, seg_len, shift, dst, next, tasks, list_stride, base_big,
+                             base_task);
+        __syncthreads();
+        return;
+    }
+    __shared__ uint32_t count[3];
+    if (d < 3) count[d] = 0u;
+    __syncthreads();
+    // 2: a big segment of the next level; 0, 1: a task of that list; 3: nothing
+    const int kind = len == 0 ? 3 : len > kLocalMax ? 2 : task_list(len, (uint32_t)shift);
+    uint32_t at = 0;
+    if (kind < 3) at = atomicAdd(&count[kind], 1u);
+    __syncthreads();
+    if (d == 0) {
+        base_big = count[2] ? atomicAdd(&ctl->n_big[cur ^ 1], count[2]) : 0u;
+        for (int l = 0; l < 2; ++l) base_task[l] = count[l] ? atomicAdd(&ctl->n_tasks[l], count[l]) : 0u;
+    }
+    __syncthreads();
+    if (kind == 2)
+        next[base_big + at] = Seg{st[d], len, 0u, 0u};
+    else if (kind < 2)
+        tasks[(int64_t)kind * list_stride + base_task[kind] + at] = Task{st[d], len, (uint32_t)shift, dst};
+    __syncthreads();
+}
+
 // Level 0 done by the plain partition pass (the whole input is one segment):
 // its partition offsets (part[d], part[256] = n) become the first level's
 // sub-segments.  One workgroup of 256 threads; also resets the counters.
@@ -260,7 +290,7 @@ __global__ __launch_bounds__(kAuxBlock) void msb_level0_kernel(Ctl *ctl, const u
     }
     __syncthreads();
     // big sub-segments go to list 1, which level 1 reads
-    if (d == 0) plan_subsegments(ctl, 0, st, tot, 0u, n, 24, 1u, next, tasks, list_stride, base_big, base_task);
+    plan_segment(ctl, 0, st, tot, 0u, n, 24, 1u, next, tasks, list_stride, base_big, base_task);
 }
 
 // One workgroup per big segment (thread d = digit d): the chunks' counts
@@ -277,30 +307,40 @@ __global__ __launch_bounds__(kAuxBlock) void msb_scan_kernel(Ctl *ctl, const Seg
     const uint32_t nb = ctl->n_big[cur];
     for (uint32_t i = blockIdx.x; i < nb; i += gridDim.x) {
         const Seg s = big[i];
+        // the chunks' counts of this digit, kAhead loads in flight: their sum, then their prefixes
+        constexpr uint32_t kAhead = 16;
+        uint32_t *col = hist + (int64_t)s.chunk_base * kBins + d;
         uint32_t run = 0;
-        for (uint32_t j = 0; j < s.nchunks; ++j) {
-            uint32_t *p = hist + (int64_t)(s.chunk_base + j) * kBins + d;
-            const uint32_t v = *p;
-            *p = run;
-            run += v;
+        for (uint32_t j = 0; j < s.nchunks; j += kAhead) {
+            uint32_t v[kAhead];
+#pragma unroll
+            for (uint32_t k = 0; k < kAhead; ++k) v[k] = j + k < s.nchunks ? col[(int64_t)(j + k) * kBins] : 0u;
+#pragma unroll
+            for (uint32_t k = 0; k < kAhead; ++k) run += v[k];
         }
         uint32_t unused;
         const uint32_t dstart = block_scan_excl<kAuxBlock>(run, tmp, unused);
         const uint32_t at = s.start + dstart;
-        for (uint32_t j = 0; j < s.nchunks; ++j) hist[(int64_t)(s.chunk_base + j) * kBins + d] += at;
+        uint32_t next_at = at;
+        for (uint32_t j = 0; j < s.nchunks; j += kAhead) {
+            uint32_t v[kAhead];
+#pragma unroll
+            for (uint32_t k = 0; k < kAhead; ++k) v[k] = j + k < s.nchunks ? col[(int64_t)(j + k) * kBins] : 0u;
+#pragma unroll
+            for (uint32_t k = 0; k < kAhead; ++k) {
+                if (j + k < s.nchunks) col[(int64_t)(j + k) * kBins] = next_at;
+                next_at += v[k];
+            }
+        }
         st[d] = at;
         tot[d] = run;
-        __syncthreads();
-        if (d == 0)
-            plan_subsegments(ctl, cur, st, tot, s.start, s.len, shift, dst, next, tasks, list_stride, base_big,
-                             base_task);
-        __syncthreads();
+        plan_segment(ctl, cur, st, tot, s.start, s.len, shift, dst, next, tasks, list_stride, base_big, base_task);
     }
 }
 
 // ---------------------------------------------------------------- shuffle --
 template <bool VALS>
-__global__ __launch_bounds__(kPartBlock, 8) void msb_shuffle_kernel(const Ctl *ctl, const ChunkD *chunks,
+__global__ __launch_bounds__(kPartBlock, 8) void msb_shuffle_kernel(Ctl *ctl, const ChunkD *chunks,
                                                                     const uint32_t *__restrict__ hist,
                                                                     const uint32_t *__restrict__ ik,
                                                                     const uint32_t *__restrict__ iv,
@@ -309,13 +349,22 @@ __global__ __launch_bounds__(kPartBlock, 8) void msb_shuffle_kernel(const Ctl *c
     using RT = RadixTile<kPartBlock, kPartIpt>;
     extern __shared__ uint32_t lds[];
     uint32_t *s_run = lds + RT::RUN;
+    // the chunks of an XCD's workgroups are consecutive (see xcd_item; the grid
+    // is a multiple of 8) and are taken in order, so that neighbours are written
+    // at about the same time
+    __shared__ uint32_t s_next[2];
     const uint32_t nc = ctl->n_chunks;
-    for (uint32_t c = blockIdx.x; c < nc; c += gridDim.x) {
+    const uint32_t x = blockIdx.x % 8, wgs = gridDim.x / 8;
+    const uint32_t first = (uint32_t)((uint64_t)nc * x / 8), last = (uint32_t)((uint64_t)nc * (x + 1) / 8);
+    uint32_t c = first + blockIdx.x / 8;
+    for (int turn = 0; c < last; turn ^= 1) {
         const ChunkD ch = chunks[c];
+        if (threadIdx.x == 0) s_next[turn] = first + wgs + atomicAdd(&ctl->taken[x], 1u);
         // the previous chunk last used s_run before its scatter barrier
         if (threadIdx.x < kBins) s_run[threadIdx.x] = hist[(int64_t)c * kBins + threadIdx.x];
         __syncthreads();
         shuffle_range<kPartBlock, kPartIpt, VALS, true>(ik, iv, ch.start, ch.end, shift, 0xFFu, ok, ov, lds);
+        c = s_next[turn];
     }
 }
 
@@ -334,11 +383,7 @@ __global__ __launch_bounds__(BLOCK, 8) void msb_local_kernel(const Ctl *ctl, int
                                                              const uint32_t *__restrict__ tmp_v) {
     using RT = RadixTile<BLOCK, IPT>;
     extern __shared__ uint32_t lds[];
-    uint32_t *stage = lds + RT::STAGE;
-    uint16_t *wc = reinterpret_cast<uint16_t *>(lds + RT::WC);
     const int tid = threadIdx.x;
-    const int w = tid / kWave;
-    uint16_t *my_wc = wc + w * kBins;
     const int off0 = RT::offset(0);
     const uint32_t nt = ctl->n_tasks[list];
     auto src_k = [&](const Task &t) { return t.src == 0 ? in_k : t.src == 1 ? (const uint32_t *)out_k : tmp_k; };
@@ -361,49 +406,32 @@ __global__ __launch_bounds__(BLOCK, 8) void msb_local_kernel(const Ctl *ctl, int
         uint32_t key[IPT], val[IPT];
         load_tile<BLOCK, IPT, false>(src_k(task) + task.start, 0, len, off0, key);
         if (VALS) load_tile<BLOCK, IPT, false>(src_v(task) + task.start, 0, len, off0, val);
-        for (uint32_t sh = 0; sh < task.bits; sh += 8) {
-            const uint32_t left = task.bits - sh;
-            const uint32_t mask = left >= 8 ? 0xFFu : (1u << left) - 1u;
-            Pos16<IPT> pos;
-            clear_counters(my_wc);
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int k = 0; k < IPT; ++k) {
-                pos.init(k, stable_rank(digit_of(key[k], (int)sh, mask), my_wc));
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            __syncthreads();
-            if (w == 0) {
-                uint32_t start[4], cnt[4];
-                scan_counters<RT::W>(wc, start, cnt);
-            }
-            __syncthreads();
-            place_keys<IPT>(key, (int)sh, mask, my_wc, pos, stage);
-            __syncthreads();
-            const bool last = sh + 8 >= task.bits;
-            if (last) {
-                for (int i = tid; i < len; i += BLOCK) out_k[task.start + i] = stage[i];
-            } else {
-#pragma unroll
-                for (int k = 0; k < IPT; ++k) key[k] = stage[off0 + k * kWave];
-            }
-            if constexpr (VALS) {
-                __syncthreads();
-#pragma unroll
-                for (int k = 0; k < IPT; ++k) stage[pos.get(k)] = val[k];
-                __syncthreads();
-                if (last) {
-                    for (int i = tid; i < len; i += BLOCK) out_v[task.start + i] = stage[i];
-                } else {
-#pragma unroll
-                    for (int k = 0; k < IPT; ++k) val[k] = stage[off0 + k * kWave];
-                }
-            }
-            // no barrier: the stage is written again only after the next
-            // ranking barrier, and a wave's counters were last read by the
-            // wave itself
-        }
+        sort_in_lds<BLOCK, IPT, VALS>(key, val, len, task.bits, out_k + task.start,
+                                      VALS ? out_v + task.start : nullptr, lds);
     }
+}
+
+// A short input in one workgroup.
+template <bool VALS, int BLOCK, int IPT>
+__global__ __launch_bounds__(BLOCK) void sort_short_kernel(const uint32_t *__restrict__ in_k,
+                                                           const uint32_t *__restrict__ in_v, int n,
+                                                           uint32_t *__restrict__ out_k,
+                                                           uint32_t *__restrict__ out_v) {
+    using RT = RadixTile<BLOCK, IPT>;
+    __shared__ __align__(16) uint32_t lds[RT::WORDS];
+    uint32_t key[IPT], val[IPT];
+    load_tile<BLOCK, IPT, false>(in_k, 0, n, RT::offset(0), key);
+    if (VALS) load_tile<BLOCK, IPT, false>(in_v, 0, n, RT::offset(0), val);
+    sort_in_lds<BLOCK, IPT, VALS>(key, val, n, 32u, out_k, out_v, lds);
+}
+
+template <bool VALS>
+hipError_t sort_short(const uint32_t *keys, const uint32_t *vals, int n, uint32_t *ok, uint32_t *ov, hipStream_t s) {
+    if (n <= 2048)
+        hipLaunchKernelGGL((sort_short_kernel<VALS, 1024, 2>), dim3(1), dim3(1024), 0, s, keys, vals, n, ok, ov);
+    else
+        hipLaunchKernelGGL((sort_short_kernel<VALS, 1024, 8>), dim3(1), dim3(1024), 0, s, keys, vals, n, ok, ov);
+    return hipGetLastError();
 }
 
 int64_t r256(int64_t b) { return (b + 255) / 256 * 256; }
@@ -416,16 +444,18 @@ struct MsbLayout {
 MsbLayout msb_layout(int64_t n, bool vals) {
     MsbLayout L{};
     L.max_big = n / (kLocalMax + 1) > 1 ? n / (kLocalMax + 1) : 1;
-    L.max_chunks = n / kChunk + L.max_big + 1;
+    // a big segment of up to kChunk = 2 kLocalMax pairs is one chunk, a longer
+    // one at most len / kLocalMax: no more than n / kLocalMax chunks
+    L.max_chunks = n / kCopy + L.max_big + 1;
     // tasks, per level with a digit left below it: one per sub-segment of
     // kSmallSeg pairs or more (at most n / kSmallSeg), and groups of shorter
     // ones; a group closes above kLocalMax - kSmallSeg pairs, before a longer
     // or a big sub-segment, or at its parent's end, so there are at most
     // n / (kLocalMax - kSmallSeg) + n / kSmallSeg + (big segments of this and
     // the next level) of them.  Then the last level's copies (pieces of at
-    // most kChunk pairs of the big segments) and the single task of a short
+    // most kCopy pairs of the big segments) and the single task of a short
     // input.
-    L.max_tasks = 3 * (2 * (n / kSmallSeg) + n / (kLocalMax - kSmallSeg) + 2 * L.max_big + 2) + n / kChunk +
+    L.max_tasks = 3 * (2 * (n / kSmallSeg) + n / (kLocalMax - kSmallSeg) + 2 * L.max_big + 2) + n / kCopy +
                   L.max_big + 8;
     int64_t at = 0;
     L.tmp_k = at;
@@ -447,7 +477,7 @@ MsbLayout msb_layout(int64_t n, bool vals) {
     L.part = at;
     at += r256((kBins + 1) * 4);
     L.pass = at;
-    at += r256(radix_pass_scratch_bytes(tune_lookup(CRYSTAL_K_RADIX, n), n));
+    at += r256(radix_pass_min_scratch_bytes(radix_long_cfg(n), n));
     L.total = at;
     return L;
 }
@@ -498,18 +528,15 @@ hipError_t msb_run(const uint32_t *keys, const uint32_t *vals, int64_t n, uint32
         return hipGetLastError();
     };
 
-    if (n <= (int64_t)kLocalMax) {
-        // one task: the whole input, sorted in LDS
-        hipLaunchKernelGGL(msb_init_kernel, dim3(1), dim3(64), 0, s, ctl, tasks, stride, (uint32_t)n);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        return local_sorts(1, 1);
-    }
     // level 0: the whole input is one segment, so the plain stable partition
     // pass on the top byte does it (input -> output), and its partition
     // offsets give the first level's sub-segments
-    const LaunchCfg rcfg = tune_lookup(CRYSTAL_K_RADIX, n);
-    e = launch_radix_partition(rcfg, keys, vals, n, 24, 8, ok, ov, (uint32_t *)(base + L.part), base + L.pass, true,
-                               s);
+    const LaunchCfg rcfg = radix_long_cfg(n);
+    // its count matrix goes where the later levels' counts will be, if it fits there
+    const bool in_hist = L.max_chunks * kBins * 4 >= radix_pass_scratch_bytes(rcfg, n);
+    e = launch_radix_partition(rcfg, keys, vals, n, 24, 8, ok, ov, (uint32_t *)(base + L.part),
+                               in_hist ? base + L.hist : base + L.pass,
+                               in_hist ? L.max_chunks * kBins * 4 : L.total - L.pass, true, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(msb_level0_kernel, dim3(1), dim3(kAuxBlock), 0, s, ctl, (const uint32_t *)(base + L.part),
                        (uint32_t)n, big[1], tasks, stride);
@@ -526,7 +553,7 @@ hipError_t msb_run(const uint32_t *keys, const uint32_t *vals, int64_t n, uint32
         hipLaunchKernelGGL(msb_hist_kernel, aux_grid, aux, 0, s, ctl, chunks, sk, shift, hist);
         hipLaunchKernelGGL(msb_scan_kernel, aux_grid, aux, 0, s, ctl, big[cur], cur, hist, big[cur ^ 1], tasks,
                            stride, shift, dst);
-        hipLaunchKernelGGL(msb_shuffle_kernel<VALS>, dim3((unsigned)(cus * part_per_cu)), dim3(kPartBlock),
+        hipLaunchKernelGGL(msb_shuffle_kernel<VALS>, dim3((unsigned)((cus * part_per_cu + 7) / 8 * 8)), dim3(kPartBlock),
                            shuffle_lds, s, ctl, chunks, hist, sk, sv, dk, dv, shift);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
@@ -534,6 +561,13 @@ hipError_t msb_run(const uint32_t *keys, const uint32_t *vals, int64_t n, uint32
 }
 
 }  // namespace
+
+hipError_t launch_sort_short(const uint32_t *keys, const uint32_t *vals, int64_t n, uint32_t *out_keys,
+                             uint32_t *out_vals, hipStream_t s) {
+    static_assert(kSortShortMax == 1024 * 8, "the larger shape holds every short input");
+    return vals ? sort_short<true>(keys, vals, (int)n, out_keys, out_vals, s)
+                : sort_short<false>(keys, nullptr, (int)n, out_keys, nullptr, s);
+}
 
 int64_t msb_sort_scratch_bytes(int64_t n, bool with_values) { return msb_layout(n, with_values).total; }
 

@@ -3,12 +3,13 @@
 // places every pair into one of 2^r contiguous partitions by the digit
 // (key >> a) & (2^r - 1).  It has the two phases of section 4.4:
 //
-//   histogram  each workgroup counts the digits of its contiguous chunk of
-//              the input; one small kernel turns the digit x workgroup count
-//              matrix into exclusive prefixes (digit-major), which are the
-//              output offsets of every (digit, workgroup) run;
-//   shuffle    each workgroup walks its chunk tile by tile and writes every
-//              pair to its partition, advancing one running offset per digit.
+//   histogram  workgroups count the digits of tiles, or of chunks of several
+//              tiles; one small kernel turns the digit x column count matrix
+//              into exclusive prefixes (digit-major), which are the output
+//              offsets of every (digit, column) run; for few tiles the shuffle
+//              sums the counts itself;
+//   shuffle    each workgroup writes the pairs of its tile, or of its chunk
+//              tile by tile, to their partitions (radix_tile.hpp).
 //
 // The shuffle is stable, also for 8-bit digits.  Within a tile each wave
 // ranks its items per digit with ballots: the lanes whose digit equals the
@@ -19,12 +20,6 @@
 // write consecutive addresses of one partition.  The section's GPU designs
 // keep per-thread digit counters in registers, which limits a stable pass to
 // 7 bits; the wave-level ranking needs no per-thread counters.
-//
-// Tile layout: a tile is BLOCK x IPT items; wave w owns the 64 * IPT
-// consecutive items starting at w * 64 * IPT, and lane l's slot k is item
-// k * 64 + l of that segment.  Processing slots in k order therefore visits
-// a wave's items in input order, which is what makes the ranking stable.
-// Every load instruction of a wave reads 256 consecutive bytes.
 #include "block.hpp"
 #include "internal.hpp"
 #include "radix_tile.hpp"
@@ -76,14 +71,17 @@ __device__ __forceinline__ Chunk chunk_of(int64_t col, int sub, int64_t tiles_pe
 // ------------------------------------------------------------- histogram --
 // Column c of the count matrix counts the digits of sub-chunk c (sub-chunks
 // split each shuffle workgroup's chunk `sub` ways, in order; chunks are whole
-// shuffle tiles of tile_items items).  MATRIX: write counts[d * cols + c];
-// otherwise add into the global histogram counts[d].  The counting workgroup
+// shuffle tiles of tile_items items).  MODE kMatrix: write counts[d * cols + c];
+// kRows (a tile per column): write 16-bit counts[c * 256 + d]; kTotals: add into
+// the global histogram counts[d].  The counting workgroup
 // has its own shape: kHistBlock threads reading kHistIpt coalesced words each
 // per step, with one LDS digit histogram per wave.
 constexpr int kHistBlock = 256;
 constexpr int kHistIpt = 16;
 
-template <bool MATRIX>
+enum HistMode { kMatrix, kRows, kTotals };
+
+template <HistMode MODE>
 __global__ __launch_bounds__(kHistBlock) void radix_hist_kernel(const uint32_t *__restrict__ keys, int64_t n,
                                                                 int shift, uint32_t mask, int64_t tile_items,
                                                                 int64_t n_tiles, int64_t tiles_per_block, int sub,
@@ -94,7 +92,8 @@ __global__ __launch_bounds__(kHistBlock) void radix_hist_kernel(const uint32_t *
     for (int i = threadIdx.x; i < W * kBins; i += kHistBlock) (&h[0][0])[i] = 0u;
     __syncthreads();
     const int w = threadIdx.x / kWave;
-    const Chunk ch = chunk_of(blockIdx.x, sub, tiles_per_block, n_tiles);
+    const int64_t col = xcd_item(blockIdx.x, gridDim.x);
+    const Chunk ch = chunk_of(col, sub, tiles_per_block, n_tiles);
     const int64_t i0 = ch.t0 * tile_items;
     int64_t i1 = ch.t1 * tile_items;
     if (i1 > n) i1 = n;
@@ -138,10 +137,14 @@ __global__ __launch_bounds__(kHistBlock) void radix_hist_kernel(const uint32_t *
         uint32_t s = 0;
 #pragma unroll
         for (int i = 0; i < W; ++i) s += h[i][d];
-        if (MATRIX)
-            counts[(int64_t)d * cols + blockIdx.x] = s;
+        if (MODE == kMatrix)
+            counts[(int64_t)d * cols + col] = s;
+        else if (MODE == kRows)
+            reinterpret_cast<uint16_t *>(counts)[col * kBins + d] = (uint16_t)s;
         else if (s)
             atomicAdd(&counts[d], s);
+    } else if (MODE == kRows && d < kBins) {
+        reinterpret_cast<uint16_t *>(counts)[col * kBins + d] = 0;
     }
 }
 
@@ -151,19 +154,27 @@ constexpr int kScanBlock = 1024;
 __global__ __launch_bounds__(kScanBlock) void radix_scan_kernel(uint32_t *__restrict__ counts, int64_t cols,
                                                                 uint32_t *__restrict__ totals) {
     __shared__ uint32_t tmp[kScanBlock / kWave];
+    // rounds of kScanBlock * kAhead columns, neighbouring threads on neighbouring
+    // words (16,384 columns: 51 -> 18 us against a run of columns per thread)
+    constexpr int kAhead = 4;
     uint32_t *row = counts + (int64_t)blockIdx.x * cols;
-    const int64_t per = (cols + kScanBlock - 1) / kScanBlock;
-    const int64_t c0 = (int64_t)threadIdx.x * per;
-    int64_t c1 = c0 + per;
-    if (c1 > cols) c1 = cols;
-    uint32_t s = 0;
-    for (int64_t c = c0; c < c1; ++c) s += row[c];
-    uint32_t total;
-    uint32_t run = block_exclusive_scan_u32<kScanBlock>(s, tmp, total);
-    for (int64_t c = c0; c < c1; ++c) {
-        uint32_t v = row[c];
-        row[c] = run;
-        run += v;
+    uint32_t total = 0;
+    for (int64_t c0 = 0; c0 < cols; c0 += kScanBlock * kAhead) {
+        uint32_t v[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const int64_t c = c0 + k * kScanBlock + (int64_t)threadIdx.x;
+            v[k] = c < cols ? row[c] : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            const int64_t c = c0 + k * kScanBlock + (int64_t)threadIdx.x;
+            if (c0 + k * kScanBlock >= cols) break;
+            uint32_t sum;
+            const uint32_t before = block_exclusive_scan_u32<kScanBlock>(v[k], tmp, sum);
+            if (c < cols) row[c] = total + before;
+            total += sum;
+        }
     }
     if (threadIdx.x == 0) totals[blockIdx.x] = total;
 }
@@ -185,19 +196,66 @@ __global__ __launch_bounds__(BLOCK, 8) void radix_shuffle_kernel(
     extern __shared__ uint32_t lds[];
     uint32_t *s_run = lds + RT::RUN;
     const int tid = threadIdx.x;
+    const int64_t block = xcd_item(blockIdx.x, gridDim.x);
 
-    // partition starts: exclusive prefix of the digit totals (the stage is free as scratch)
-    uint32_t unused;
-    const uint32_t tot = (tid < kBins && (uint32_t)tid <= mask) ? totals[tid] : 0u;
-    const uint32_t dstart = block_exclusive_scan_u32<BLOCK>(tot, lds, unused);
-    if (tid < kBins) {
-        s_run[tid] = (uint32_t)tid <= mask ? dstart + counts[(int64_t)tid * cols + (int64_t)blockIdx.x * sub] : 0u;
-        if (blockIdx.x == 0 && part_offsets && (uint32_t)tid <= mask) part_offsets[tid] = dstart;
+    if (totals) {
+        // partition starts: exclusive prefix of the digit totals (the stage is free as scratch)
+        uint32_t unused;
+        const uint32_t tot = (tid < kBins && (uint32_t)tid <= mask) ? totals[tid] : 0u;
+        const uint32_t dstart = block_exclusive_scan_u32<BLOCK>(tot, lds, unused);
+        if (tid < kBins) {
+            s_run[tid] = (uint32_t)tid <= mask ? dstart + counts[(int64_t)tid * cols + block * sub] : 0u;
+            if (block == 0 && part_offsets && (uint32_t)tid <= mask) part_offsets[tid] = dstart;
+        }
+    } else {
+        // few tiles: the rows of counts are summed here, each wave every W-th
+        // row, a lane four digits (see kRows); no scan launch
+        uint32_t *s_tot = lds + RT::GBASE;
+        if (tid < kBins) s_run[tid] = s_tot[tid] = 0u;
+        __syncthreads();
+        const uint2 *rows = reinterpret_cast<const uint2 *>(counts) + lane_id();
+        uint32_t tot[4] = {0u, 0u, 0u, 0u}, before[4] = {0u, 0u, 0u, 0u};
+        constexpr int kAhead = 8;
+        for (int64_t c0 = tid / kWave; c0 < cols; c0 += kAhead * RT::W) {
+            uint2 v[kAhead];
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                const int64_t c = c0 + k * RT::W;
+                v[k] = c < cols ? rows[c * (kBins / 4)] : make_uint2(0u, 0u);
+            }
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                const uint32_t x[4] = {v[k].x & 0xffffu, v[k].x >> 16, v[k].y & 0xffffu, v[k].y >> 16};
+                const bool earlier = c0 + k * RT::W < block;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    tot[i] += x[i];
+                    before[i] += earlier ? x[i] : 0u;
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            atomicAdd(&s_tot[4 * lane_id() + i], tot[i]);
+            atomicAdd(&s_run[4 * lane_id() + i], before[i]);
+        }
+        __syncthreads();
+        if (tid < kWave) {
+            const uint4 t = reinterpret_cast<uint4 *>(s_tot)[tid];
+            uint32_t at = t.x + t.y + t.z + t.w;
+            at = wave_inclusive_scan(at) - at;
+            const uint32_t start[4] = {at, at + t.x, at + t.x + t.y, at + t.x + t.y + t.z};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                s_run[4 * tid + i] += start[i];
+                if (block == 0 && part_offsets && (uint32_t)(4 * tid + i) <= mask) part_offsets[4 * tid + i] = start[i];
+            }
+        }
     }
-    if (blockIdx.x == 0 && part_offsets && tid == 0) part_offsets[mask + 1] = (uint32_t)n;
+    if (block == 0 && part_offsets && tid == 0) part_offsets[mask + 1] = (uint32_t)n;
     __syncthreads();
 
-    const int64_t t0 = (int64_t)blockIdx.x * tiles_per_block;
+    const int64_t t0 = block * tiles_per_block;
     int64_t t1 = t0 + tiles_per_block;
     if (t1 > n_tiles) t1 = n_tiles;
     if (t0 >= t1) return;
@@ -209,6 +267,7 @@ __global__ __launch_bounds__(BLOCK, 8) void radix_shuffle_kernel(
 struct RadixGeom {
     int64_t n_tiles, tiles_per_block, grid, cols;
     int sub;
+    bool rows;  // counts as kRows, summed by the shuffle
 };
 
 template <int BLOCK, int IPT>
@@ -224,16 +283,11 @@ struct RadixKernels {
         return e;
     }
 
+    template <HistMode MODE>
     static hipError_t histogram(const uint32_t *keys, int64_t n, int shift, uint32_t mask, const RadixGeom &g,
-                                uint32_t *counts, bool matrix, hipStream_t s) {
-        const dim3 grid((unsigned)(g.grid * g.sub)), block(kHistBlock);
-        const int64_t items = (int64_t)BLOCK * IPT;
-        if (matrix)
-            hipLaunchKernelGGL((radix_hist_kernel<true>), grid, block, 0, s, keys, n, shift, mask, items,
-                               g.n_tiles, g.tiles_per_block, g.sub, counts, g.cols);
-        else
-            hipLaunchKernelGGL((radix_hist_kernel<false>), grid, block, 0, s, keys, n, shift, mask, items,
-                               g.n_tiles, g.tiles_per_block, g.sub, counts, g.cols);
+                                uint32_t *counts, hipStream_t s) {
+        hipLaunchKernelGGL((radix_hist_kernel<MODE>), dim3((unsigned)(g.grid * g.sub)), dim3(kHistBlock), 0, s, keys,
+                           n, shift, mask, (int64_t)BLOCK * IPT, g.n_tiles, g.tiles_per_block, g.sub, counts, g.cols);
         return hipGetLastError();
     }
 
@@ -272,16 +326,42 @@ size_t shuffle_lds_bytes(int block, int ipt) {
     }
 }
 
-// Workgroups of the shuffle kernel per CU: the tuned value, else as many as
-// the LDS allows (at most 8).
-RadixGeom geometry(const LaunchCfg &cfg, int64_t n) {
+// Up to so many tiles the shuffle sums the counts of earlier tiles itself,
+// which saves the scan launch (four passes over 100,003 pairs 57 -> 45 us;
+// 244 tiles 66 -> 62 us; 490 tiles 75 -> 84 us).
+constexpr int64_t kRowsMax = 256;
+
+// Scratch of a pass with a count per tile: kRows, or as below.
+int64_t rows_bytes(int64_t tiles) { return tiles * kBins * 2; }
+
+// Scratch of a pass under g: the count matrix (kBins rows of cols words,
+// 256-byte aligned) and the digit totals.
+int64_t pass_bytes(int64_t cols) { return ((int64_t)kBins * cols * 4 + 255) / 256 * 256 + kBins * 4; }
+
+int64_t fine_bytes(int64_t tiles) { return tiles <= kRowsMax ? rows_bytes(tiles) : pass_bytes(tiles); }
+
+// One tile per workgroup when the scratch holds a count per tile and no grid
+// was tuned: then neighbouring tiles are written at the same time on one XCD
+// (xcd_item).  Shuffle of 2^28 pairs: 1,400 us with 32 tiles per workgroup,
+// 1,080 us so.  Else workgroups of several tiles, a tuned number per CU or by the
+// LDS (at most 8).
+RadixGeom geometry(const LaunchCfg &cfg, int64_t n, int64_t scratch_bytes) {
     RadixGeom g{};
     const int64_t items = (int64_t)cfg.block * cfg.ipt;
     g.n_tiles = (n + items - 1) / items;
+    if (cfg.grid_per_cu <= 0 && scratch_bytes >= fine_bytes(g.n_tiles)) {
+        g.grid = g.cols = g.n_tiles;
+        g.tiles_per_block = 1;
+        g.sub = 1;
+        g.rows = g.n_tiles <= kRowsMax;
+        return g;
+    }
     int per_cu = cfg.grid_per_cu;
     if (per_cu <= 0) {
-        const size_t lds = shuffle_lds_bytes(cfg.block, cfg.ipt);
-        per_cu = lds ? (int)(device_lds_per_cu() / (int64_t)lds) : 1;
+        // half of what the LDS holds (a tile twice, and its counters): chunks
+        // gain nothing from more (2^28 pairs 1,628 us, with twice as many 1,643)
+        const int64_t waves = cfg.block / kWave;
+        per_cu = (int)(device_lds_per_cu() / (4 * (2 * items + waves * (kBins + 1) + 2 * kBins)));
         if (per_cu < 1) per_cu = 1;
         if (per_cu > 8) per_cu = 8;
     }
@@ -303,11 +383,14 @@ RadixGeom geometry(const LaunchCfg &cfg, int64_t n) {
 
 }  // namespace
 
-// Scratch of one partition pass: the count matrix (kBins rows of cols words,
-// 256-byte aligned) and the digit totals.
+int64_t radix_pass_min_scratch_bytes(const LaunchCfg &cfg, int64_t n) {
+    return pass_bytes(geometry(cfg, n > 0 ? n : 1, 0).cols);
+}
+
 int64_t radix_pass_scratch_bytes(const LaunchCfg &cfg, int64_t n) {
-    const RadixGeom g = geometry(cfg, n > 0 ? n : 1);
-    return ((int64_t)kBins * g.cols * 4 + 255) / 256 * 256 + kBins * 4;
+    const int64_t items = (int64_t)cfg.block * cfg.ipt;
+    if (cfg.grid_per_cu > 0) return radix_pass_min_scratch_bytes(cfg, n);
+    return fine_bytes(((n > 0 ? n : 1) + items - 1) / items);
 }
 
 bool radix_variant_fits(int block, int ipt) {
@@ -326,32 +409,44 @@ hipError_t launch_radix_histogram(const LaunchCfg &cfg, const uint32_t *keys, in
     const uint32_t mask = (1u << bits) - 1u;
     hipError_t e = fill_u32(hist, (int64_t)mask + 1, 0u, s);
     if (e != hipSuccess || n == 0) return e;
-    const RadixGeom g = geometry(cfg, n);
+    const RadixGeom g = geometry(cfg, n, 0);
 #define X(B, I) \
-    case CRYSTAL_VARIANT_KEY(B, I): return RadixKernels<B, I>::histogram(keys, n, shift, mask, g, hist, false, s);
+    case CRYSTAL_VARIANT_KEY(B, I): return RadixKernels<B, I>::template histogram<kTotals>(keys, n, shift, mask, g, hist, s);
     RADIX_DISPATCH(cfg, X)
 #undef X
 }
 
 hipError_t launch_radix_partition(const LaunchCfg &cfg, const uint32_t *keys, const uint32_t *vals, int64_t n,
                                   int shift, int bits, uint32_t *out_keys, uint32_t *out_vals,
-                                  uint32_t *part_offsets, void *scratch, bool stable, hipStream_t s) {
+                                  uint32_t *part_offsets, void *scratch, int64_t scratch_bytes, bool stable,
+                                  hipStream_t s) {
     const uint32_t mask = (1u << bits) - 1u;
     if (n == 0) return part_offsets ? fill_u32(part_offsets, (int64_t)mask + 2, 0u, s) : hipSuccess;
-    const RadixGeom g = geometry(cfg, n);
+    const RadixGeom g = geometry(cfg, n, scratch_bytes);
     uint32_t *counts = (uint32_t *)scratch;
     uint32_t *totals = (uint32_t *)((char *)scratch + ((int64_t)kBins * g.cols * 4 + 255) / 256 * 256);
     hipError_t e;
-#define X(B, I)                                                                                     \
-    case CRYSTAL_VARIANT_KEY(B, I):                                                                 \
-        e = RadixKernels<B, I>::histogram(keys, n, shift, mask, g, counts, true, s);                \
+    if (g.rows) {
+        totals = nullptr;  // the shuffle sums the rows itself
+#define X(B, I)                                                                                         \
+    case CRYSTAL_VARIANT_KEY(B, I):                                                                     \
+        e = RadixKernels<B, I>::template histogram<kRows>(keys, n, shift, mask, g, counts, s);          \
         break;
-    RADIX_DISPATCH(cfg, X)
+        RADIX_DISPATCH(cfg, X)
 #undef X
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(radix_scan_kernel, dim3(mask + 1), dim3(kScanBlock), 0, s, counts, g.cols, totals);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+        if (e != hipSuccess) return e;
+    } else {
+#define X(B, I)                                                                                         \
+    case CRYSTAL_VARIANT_KEY(B, I):                                                                     \
+        e = RadixKernels<B, I>::template histogram<kMatrix>(keys, n, shift, mask, g, counts, s);        \
+        break;
+        RADIX_DISPATCH(cfg, X)
+#undef X
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(radix_scan_kernel, dim3(mask + 1), dim3(kScanBlock), 0, s, counts, g.cols, totals);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
 #define X(B, I)                                                                                              \
     case CRYSTAL_VARIANT_KEY(B, I):                                                                          \
         return RadixKernels<B, I>::shuffle(keys, vals, n, shift, mask, g, counts, totals, out_keys, out_vals, \

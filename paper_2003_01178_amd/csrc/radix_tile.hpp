@@ -43,6 +43,16 @@ struct RadixTile {
     }
 };
 
+// Work item of workgroup b of n, such that the workgroups of an XCD (consecutive
+// workgroups go round the eight XCDs) get consecutive items.  A tile's run in a
+// partition rarely ends at a 128-byte line; the next tile continues the line, and
+// when that is on the same XCD at about the same time the line leaves its L2
+// whole.  Only speed depends on the placement.
+__device__ __forceinline__ int64_t xcd_item(int64_t b, int64_t n) {
+    const int64_t q = n / 8, r = n % 8, x = b % 8;
+    return x * q + (x < r ? x : r) + b / 8;
+}
+
 __device__ __forceinline__ uint32_t digit_of(uint32_t key, int shift, uint32_t mask) { return (key >> shift) & mask; }
 
 // Inclusive prefix over the 64 lanes of a wave.
@@ -279,6 +289,62 @@ __device__ __forceinline__ void shuffle_range(const uint32_t *__restrict__ keys,
         }
         // no barrier: the next tile writes s_gbase, s_run and the stage only
         // after its ranking barrier, which every wave reaches after this write-out
+    }
+}
+
+// Sort of a tile: the items key (and val), `len` of them in tile layout, by
+// their low `bits` key bits with stable 8-bit passes, written to out_k (out_v).
+template <int BLOCK, int IPT, bool VALS>
+__device__ __forceinline__ void sort_in_lds(uint32_t (&key)[IPT], uint32_t (&val)[IPT], int len, uint32_t bits,
+                                            uint32_t *__restrict__ out_k, uint32_t *__restrict__ out_v,
+                                            uint32_t *lds) {
+    using RT = RadixTile<BLOCK, IPT>;
+    uint32_t *stage = lds + RT::STAGE;
+    uint16_t *wc = reinterpret_cast<uint16_t *>(lds + RT::WC);
+    const int tid = (int)threadIdx.x;
+    const int w = tid / kWave;
+    uint16_t *my_wc = wc + w * kBins;
+    const int off0 = RT::offset(0);
+    for (uint32_t sh = 0; sh < bits; sh += 8) {
+        const uint32_t left = bits - sh;
+        const uint32_t mask = left >= 8 ? 0xFFu : (1u << left) - 1u;
+        Pos16<IPT> pos;
+        clear_counters(my_wc);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) {
+            pos.init(k, stable_rank(digit_of(key[k], (int)sh, mask), my_wc));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+        if (w == 0) {
+            uint32_t start[4], cnt[4];
+            scan_counters<RT::W>(wc, start, cnt);
+        }
+        __syncthreads();
+        place_keys<IPT>(key, (int)sh, mask, my_wc, pos, stage);
+        __syncthreads();
+        const bool last = sh + 8 >= bits;
+        if (last) {
+            for (int i = tid; i < len; i += BLOCK) out_k[i] = stage[i];
+        } else {
+#pragma unroll
+            for (int k = 0; k < IPT; ++k) key[k] = stage[off0 + k * kWave];
+        }
+        if constexpr (VALS) {
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < IPT; ++k) stage[pos.get(k)] = val[k];
+            __syncthreads();
+            if (last) {
+                for (int i = tid; i < len; i += BLOCK) out_v[i] = stage[i];
+            } else {
+#pragma unroll
+                for (int k = 0; k < IPT; ++k) val[k] = stage[off0 + k * kWave];
+            }
+        }
+        // no barrier: the stage is written again only after the next ranking
+        // barrier, and a wave's counters were last read by the wave itself
     }
 }
 

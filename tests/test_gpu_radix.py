@@ -323,3 +323,83 @@ def test_unstable_partition_skewed_and_shapes(block, ipt):
                  rng.integers(0, 3, size=n, dtype=np.uint64).astype(np.uint32),
                  rng.integers(0, 2 ** 32, size=n, dtype=np.uint64).astype(np.uint32)):
         check_unstable(keys, np.arange(n, dtype=np.uint32), 0, 8)
+
+
+# ------------------------------------------------- tile counts, short inputs --
+def tricky_pairs(n, seed, key_bits=32):
+    """Random keys with runs of the largest and smallest one, also at the end."""
+    rng = np.random.default_rng(seed)
+    k = rng.integers(0, 1 << key_bits, size=n, dtype=np.uint64).astype(np.uint32)
+    k[rng.random(n) < 0.05] = 0xFFFFFFFF
+    k[rng.random(n) < 0.05] = 0
+    k[n - min(n, 70):n - min(n, 3)] = 0xFFFFFFFF
+    return k, np.arange(n, dtype=np.uint32)
+
+
+@pytest.mark.parametrize("msb", [False, True])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1024, 2047, 2048, 2049, 8191, 8192, 8193])
+def test_sort_of_short_inputs(n, msb):
+    """One workgroup sorts up to 8,192 pairs (two shapes); 8,193 take passes."""
+    announce("radix short", n, msb)
+    k, v = tricky_pairs(n, 600 + n)
+    wk, wv = oracle.sort_pairs(k, v)
+    ok, ov = cx.sort_pairs(dev(k.view(np.int32)), dev(v.view(np.int32)), msb=msb)
+    assert np.array_equal(u32(ok, n), wk) and np.array_equal(u32(ov, n), wv)
+    ok, _ = cx.sort_pairs(dev(k.view(np.int32)), msb=msb)
+    assert np.array_equal(u32(ok, n), wk)
+
+
+@pytest.mark.parametrize("n", [1 << 16, (1 << 16) + 1, 1 << 18, (1 << 18) + 1, 1 << 20, (1 << 20) + 1, (1 << 23) + 16_385])
+def test_sort_and_partition_around_shape_changes(n):
+    """Tile counts at which the shape changes, the shuffle sums the counts
+    itself (up to 256 tiles) or a scan does, and the last tile is one item."""
+    announce("radix shapes", n)
+    k, v = tricky_pairs(n, 700 + n % 97)
+    wk, wv = oracle.sort_pairs(k, v)
+    ok, ov = cx.sort_pairs(dev(k.view(np.int32)), dev(v.view(np.int32)))
+    assert np.array_equal(u32(ok, n), wk) and np.array_equal(u32(ov, n), wv)
+    for shift, bits in ((24, 8), (13, 5)):
+        check_partition(k, v, shift, bits, True)
+    check_unstable(k, v, 27, 5)
+
+
+@pytest.mark.parametrize("msb", [False, True])
+def test_sort_with_the_least_scratch(msb):
+    """Two copies and the counts of 16,384-item tiles are accepted (the
+    library asks for more), one byte less is not."""
+    lib = cx.load()
+    n = 100_003
+    k, v = tricky_pairs(n, 811)
+    copies = 2 * ((4 * n + 255) // 256 * 256)
+    tiles = -(-n // 16_384)
+    least = copies + (tiles * 1024 + 255) // 256 * 256 + 1024
+    if msb:
+        least = lib.crystal_sort_pairs_msb_scratch_bytes(n, 1)
+    else:
+        assert lib.crystal_sort_pairs_scratch_bytes(n, 1) >= least
+    announce("radix least scratch", msb, least)
+    kd, vd = dev(k.view(np.int32)), dev(v.view(np.int32))
+    ok, ov = torch.empty_like(kd), torch.empty_like(vd)
+    scratch = torch.empty(least, dtype=torch.uint8, device="cuda")
+    fn = lib.crystal_sort_pairs_msb if msb else lib.crystal_sort_pairs
+    for given, want in ((least - 1, cx.ESCRATCH), (least, cx.OK)):
+        rc = fn(cx._ptr(kd), cx._ptr(vd), n, cx._ptr(ok), cx._ptr(ov), cx._ptr(scratch), given, cx._stream())
+        assert rc == want
+    wk, wv = oracle.sort_pairs(k, v)
+    assert np.array_equal(u32(ok, n), wk) and np.array_equal(u32(ov, n), wv)
+
+
+@pytest.mark.parametrize("key_bits", [32, 20, 12])
+@pytest.mark.parametrize("n", [8193, 3 * 8192 + 5, 200_003, 1_000_003, 3_000_017])
+def test_msb_levels_with_a_tuned_shape(n, key_bits):
+    """With a tuned shape inputs of these sizes are partitioned by levels:
+    whole segments, grouped short ones, one segment for several levels, and
+    (12 bits) runs of equal keys that are copied."""
+    announce("msb levels", n, key_bits)
+    cx.tune_set(cx.K_RADIX, 1024, 16, 0)
+    k, v = tricky_pairs(n, 900 + n % 89, key_bits)
+    ok, ov = cx.sort_pairs(dev(k.view(np.int32)), dev(v.view(np.int32)), msb=True)
+    wk, wv = oracle.sort_pairs(k, v)
+    assert np.array_equal(u32(ok, n), wk) and np.array_equal(u32(ov, n), wv)
+    ok, _ = cx.sort_pairs(dev(k.view(np.int32)), msb=True)
+    assert np.array_equal(u32(ok, n), wk)
