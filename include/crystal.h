@@ -91,10 +91,10 @@ crystal_status crystal_select(const int32_t *in, int64_t n, crystal_range pred,
 
 /* The same selection with the qualifying values in input order (a stable    */
 /* compaction, identical on every run).  Each tile publishes its match count */
-/* in its own status word and finds its output offset by decoupled look-back */
-/* over its predecessors' words instead of an atomic reservation; slower on  */
-/* MI355X, whose eight XCD caches are not coherent, so every look-back round */
-/* is a memory round trip.                                                   */
+/* and adds up the published counts of the tiles before it, in sums of 64    */
+/* tiles and of 64 such groups, instead of an atomic reservation; somewhat   */
+/* slower on MI355X, whose eight XCD caches are not coherent, so the wait    */
+/* for those words is a memory round trip.                                   */
 /*   scratch   device, >= crystal_select_stable_scratch_bytes(n) bytes,      */
 /*             16-byte aligned (tile status words); calls sharing it must be */
 /*             ordered on one stream                                         */

@@ -255,7 +255,7 @@ def select(x, lo, hi, out=None, count=None, stable=False, scratch=None, stream=N
     """Section 4.2 Q3: values of x with lo <= x <= hi -> (out, count tensor).
 
     stable=False: tiles land in the order of their atomic reservations;
-    stable=True: the values in input order (decoupled look-back)."""
+    stable=True: the values in input order."""
     lib = load()
     n = x.numel()
     out = torch.empty(max(n, 1), dtype=torch.int32, device=x.device) if out is None else out

@@ -14,6 +14,13 @@ __global__ __launch_bounds__(256) void fill_u64_kernel(uint64_t *__restrict__ p,
         p[i] = value;
 }
 
+// zero p[0..n) and one word elsewhere
+__global__ __launch_bounds__(256) void zero_and_word_kernel(uint64_t *__restrict__ p, int64_t n, uint64_t *word) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = 0;
+    if (i == 0) *word = 0;
+}
+
 __global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t *__restrict__ p, int64_t n,
                                                        uint32_t value) {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -46,6 +53,11 @@ hipError_t fill_u64(uint64_t *p, int64_t n, uint64_t value, hipStream_t s) {
 hipError_t fill_u32(uint32_t *p, int64_t n, uint32_t value, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)fill_grid(n)), dim3(256), 0, s, p, n, value);
+    return hipGetLastError();
+}
+
+static hipError_t zero_and_word(uint64_t *p, int64_t n, uint64_t *word, hipStream_t s) {
+    hipLaunchKernelGGL(zero_and_word_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n, word);
     return hipGetLastError();
 }
 
@@ -114,161 +126,192 @@ hipError_t copy_ranges(const uint64_t *src, uint64_t *dst, const WordRanges &ran
 //    serialise at the memory-side atomic unit (about 12 ns each on MI355X),
 //    so tiles are large (the tuned default is 1024 x 16 = 16 Ki items) to
 //    keep the reservations well below the time the column takes to stream.
-//  - stable: every tile publishes its match count in its own 64-bit status
-//    word and finds its offset by decoupled look-back over its predecessors'
-//    words (the single-pass scan of Merrill and Garland): each round the
-//    workgroup reads BLOCK predecessors' words and stops at the nearest one
-//    that holds an inclusive prefix.  Tiles then land in input order, so the
-//    output is the qualifying values in input order on every run; the status
-//    words live in memory that all XCDs see, so each round costs a memory
-//    round trip.
+//  - stable: sums on three levels.  A tile publishes its match count; the
+//    last tile of a group (64 tiles) also the group's, once it has read the
+//    others'; the last tile of a supergroup (64 groups) the supergroup's.  A
+//    tile's offset is then at most 63 words of tiles, 63 of groups and the
+//    earlier supergroups, read by one wave in one memory round trip once they
+//    are there.  Tiles land in input order, so the output is the qualifying
+//    values in input order on every run.
 //
-// Status word: bits 63..62 = 0 (nothing yet), 1 (tile count), 2 (inclusive
-// prefix); bits 61..0 = the count.  Words are read and written with
-// agent-scope atomics (coherent across XCDs).  A tile only waits for lower-
-// numbered tiles and there is one tile per workgroup, dispatched in order, so
-// the lowest unfinished tile is always running; should a predecessor still
-// never publish, the wait gives up after a bounded number of polls: that tile
-// publishes the poison prefix 2^61, every later tile inherits it and writes
-// nothing, and the last tile reports a count of -1.
-static constexpr uint64_t kStAgg = 1ull << 62;
-static constexpr uint64_t kStIncl = 2ull << 62;
-static constexpr uint64_t kStValue = (1ull << 62) - 1;
-static constexpr uint64_t kPoison = 1ull << 61;
+//    What bounds it is the wait for words that all XCDs see.  With a status
+//    word per tile only (decoupled look-back), 1,024 tiles that start together
+//    learn their offsets 64 or 512 at a time, one round trip after another,
+//    and every poll reads as many words: 64M rows, half of them qualifying,
+//    took 161 us (512 words a round, read by the whole workgroup) and 106 us
+//    (64, by one wave), 80 us so.  (Sums added up with atomics serialised on
+//    their lines: 560 us.)
+//
+// Words are read and written with agent-scope atomics (coherent across XCDs)
+// and are zero before the launch.  There is one tile per workgroup, dispatched
+// in order, a tile publishes before it waits, and a group's and a supergroup's
+// word need only words of their own tiles and groups, so every wait ends;
+// should a predecessor still never publish, the wait gives up after a bounded
+// number of polls: the tile writes nothing and the count becomes -1.
+static constexpr uint32_t kPublished = 1u << 31;          // a tile's or group's word: this and its count
+static constexpr uint64_t kSuperPublished = 1ull << 63;
 static constexpr uint32_t kLookbackPolls = 1u << 15;
 
-__device__ __forceinline__ uint64_t status_load(const uint64_t *p) {
+// The words of n_tiles tiles, in at most 8 bytes per tile: groups are needed
+// from 65 tiles on, supergroups from 4,097.
+struct TileSums {
+    uint64_t *super;
+    uint32_t *group, *tile;
+    __host__ __device__ TileSums(void *mem, int64_t n_tiles) {
+        const int64_t ns = n_tiles > 4096 ? (n_tiles + 4095) / 4096 : 0, ng = n_tiles > 64 ? (n_tiles + 63) / 64 : 0;
+        super = (uint64_t *)mem;
+        group = (uint32_t *)(super + ns);
+        tile = group + ng;
+    }
+};
+
+template <typename W>
+__device__ __forceinline__ W word_load(const W *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void status_store(uint64_t *p, uint64_t v) {
+template <typename W>
+__device__ __forceinline__ void word_store(W *p, W v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Called by every thread of the workgroup.  Publishes the tile's count and
-// returns the number of matches in all earlier tiles (kPoison if unknown).
-// Each round, thread i reads the status word of tile top - i, so a round
-// covers BLOCK predecessors with one memory round trip; the waves' findings
-// are combined through LDS (wave_incl / wave_ready / wave_sum).
-template <int BLOCK>
-__device__ __forceinline__ uint64_t block_lookback(uint64_t *st, int64_t tile, uint64_t count,
-                                                   uint32_t *wave_flags, uint64_t *wave_sum) {
-    constexpr int W = BLOCK / kWave;
+// Called by one whole wave after the tile's own word was published: the number
+// of matches in all tiles before `tile`, or ~0 if a wait gave up.
+__device__ __forceinline__ uint64_t matches_before(const TileSums &w, int64_t tile, int64_t n_tiles, uint32_t count) {
     const uint32_t lane = lane_id();
-    const int w = threadIdx.x / kWave;
-    if (threadIdx.x == 0) status_store(st + tile, (tile == 0 ? kStIncl : kStAgg) | count);
-    if (tile == 0) return 0;
-    uint64_t running = 0;
-    bool poisoned = false;
-    int64_t top = tile - 1;
-    uint32_t polls = 0;
-    for (;;) {
-        const int64_t idx = top - (int64_t)threadIdx.x;
-        const uint64_t v = idx >= 0 ? status_load(st + idx) : kStIncl;  // before tile 0: prefix 0
-        const uint32_t flag = (uint32_t)(v >> 62);
-        const uint64_t incl = ballot(flag == 2u);
-        const uint64_t none = ballot(flag == 0u);
-        // lanes 0..stop, stop = this wave's nearest predecessor with an inclusive prefix
-        const uint64_t upto = incl ? ((incl & (~incl + 1ull)) << 1) - 1ull : ~0ull;
-        const bool mine = (upto >> lane) & 1ull;
-        const bool poison = ballot(mine && (v & kStValue) >= kPoison) != 0;
-        const uint64_t sum = wave_sum_u64(mine ? (v & kStValue) : 0ull);
-        if (lane == 0) {
-            wave_flags[w] = (incl ? 1u : 0u) | ((none & upto) ? 0u : 2u) | (poison ? 4u : 0u);
-            wave_sum[w] = sum;
+    const int64_t group = tile / 64, super = tile / 4096;
+    bool need_t = lane < (uint32_t)(tile & 63), need_g = lane < (uint32_t)(group & 63);
+    bool owe_g = (tile & 63) == 63 && n_tiles > 64, owe_s = (tile & 4095) == 4095 && n_tiles > 4096;
+    int64_t s = lane;  // this lane's next supergroup
+    uint32_t t = 0, g = 0;
+    uint64_t before = 0;
+    for (uint32_t polls = 0; polls < kLookbackPolls; ++polls) {
+        __builtin_amdgcn_s_sleep(8);  // polls that find nothing slow the stores they wait for
+        uint64_t u = 0;
+        if (need_t) t = word_load(w.tile + (tile & ~int64_t(63)) + lane);
+        if (need_g) g = word_load(w.group + (group & ~int64_t(63)) + lane);
+        if (s < super) u = word_load(w.super + s);
+        need_t = need_t && !(t & kPublished);
+        need_g = need_g && !(g & kPublished);
+        if (u & kSuperPublished) {
+            before += u & ~kSuperPublished;
+            s += kWave;
         }
-        __syncthreads();
-        // the nearest waves first: add ready waves until one holds an inclusive prefix
-        bool ready = true, done = false;
-        uint64_t add = 0;
-        for (int ww = 0; ww < W; ++ww) {
-            const uint32_t f = wave_flags[ww];
-            if (!(f & 2u)) {
-                ready = false;
-                break;
-            }
-            if (f & 4u) poisoned = true;
-            add += wave_sum[ww];
-            if (f & 1u) {
-                done = true;
-                break;
-            }
+        const bool tiles_in = ballot(need_t) == 0, groups_in = ballot(need_g) == 0;
+        if (owe_g && tiles_in) {
+            const uint32_t sum = (uint32_t)wave_sum_u64(t & ~kPublished) + count;  // at most 2^20
+            if (lane == 0) word_store(w.group + group, kPublished | sum);
+            owe_g = false;
         }
-        __syncthreads();
-        if (poisoned) break;
-        if (!ready) {
-            if (++polls > kLookbackPolls) {
-                poisoned = true;
-                break;
-            }
-            __builtin_amdgcn_s_sleep(2);
-            continue;
+        if (owe_s && tiles_in && groups_in) {
+            const uint64_t sum = wave_sum_u64((uint64_t)(t & ~kPublished) + (g & ~kPublished)) + count;
+            if (lane == 0) word_store(w.super + super, kSuperPublished | sum);
+            owe_s = false;
         }
-        running += add;
-        if (done) break;
-        top -= BLOCK;
+        if (tiles_in && groups_in && ballot(s < super) == 0)
+            return wave_sum_u64(before + (t & ~kPublished) + (g & ~kPublished));
     }
-    if (poisoned) running = kPoison;
-    if (threadIdx.x == 0) status_store(st + tile, kStIncl | (poisoned ? kPoison : running + count));
-    return running;
+    return ~0ull;
 }
 
-// Stable selection: one workgroup per tile, output offsets by decoupled look-back.
+// Store n entries of buf (LDS) to dst: scalar stores up to a 16-byte boundary,
+// vectors, then the tail.
+template <int BLOCK>
+__device__ __forceinline__ void store_run(const int32_t *buf, uint32_t n, int32_t *__restrict__ dst) {
+    uint32_t head = (uint32_t)(((16u - ((uint32_t)(uintptr_t)dst & 15u)) & 15u) >> 2);
+    if (head > n) head = n;
+    if (threadIdx.x < head) __builtin_nontemporal_store(buf[threadIdx.x], dst + threadIdx.x);
+    const uint32_t nvec = (n - head) >> 2;
+    for (uint32_t i = threadIdx.x; i < nvec; i += BLOCK) {
+        const uint32_t b = head + 4 * i;
+        const v4i x = {buf[b], buf[b + 1], buf[b + 2], buf[b + 3]};
+        __builtin_nontemporal_store(x, reinterpret_cast<v4i *>(dst + b));
+    }
+    for (uint32_t i = head + 4 * nvec + threadIdx.x; i < n; i += BLOCK) __builtin_nontemporal_store(buf[i], dst + i);
+}
+
+// Stable selection: one workgroup per tile.  A wave owns 64 * IPT consecutive
+// items, chunk by chunk of 64 vectors, so it ranks its own matches and the waves
+// exchange one total each.  In a chunk, lane l's items follow lane l - 1's: an
+// item's place is the matches of all lanes below (one ballot per item of the
+// vector, counted with mbcnt, which also adds) and of the lane's items before
+// it.  (With chunks across the workgroup the exchange of every wave's chunk
+// totals, and the scan of per-lane counts bit by bit, made the kernel bound by
+// its instructions: 103 us for 64M rows, half of them qualifying.)
 template <int BLOCK, int IPT>
 __global__ __launch_bounds__(BLOCK) void select_kernel(const int32_t *__restrict__ in, int64_t n,
-                                                       int32_t lo, int32_t hi,
-                                                       int32_t *__restrict__ out,
-                                                       uint64_t *__restrict__ st,
-                                                       int64_t *__restrict__ count_out,
+                                                       int32_t lo, int32_t hi, int32_t *__restrict__ out,
+                                                       TileSums sums, int64_t *__restrict__ count_out,
                                                        int64_t n_tiles) {
     using T = TileShape<BLOCK, IPT>;
     constexpr int C = T::CHUNKS, W = T::WAVES, V = T::VEC;
-    constexpr int VBITS = V == 1 ? 1 : V == 2 ? 2 : 3;
     __shared__ int32_t buf[T::ITEMS];
-    __shared__ uint32_t chunk_tot[C * W];
-    __shared__ uint32_t wave_flags[W];
-    __shared__ uint64_t wave_sum[W];
+    __shared__ uint32_t wave_tot[W];
+    __shared__ uint64_t out_base;
     const int w = threadIdx.x / kWave;
     const uint32_t lane = lane_id();
-    {
-        const int64_t tile = blockIdx.x;
-        const int64_t base = tile * T::ITEMS;
-        int32_t v[IPT];
-        block_load<BLOCK, IPT, true>(in, base, n, v);
-        const uint32_t flags = block_pred_range<IPT>(v, valid_mask<BLOCK, IPT>(base, n), lo, hi);
-        // BlockScan in input order: item (c, t, e) precedes (c, t', e') when t < t',
-        // and chunk c precedes chunk c + 1
-        uint32_t pre[C];
+    const int64_t tile = blockIdx.x;
+    const int64_t i0 = tile * T::ITEMS + (int64_t)w * (kWave * IPT) + (int64_t)lane * V;  // chunk 0, item 0
+    const bool full = (tile + 1) * T::ITEMS <= n;
+    int32_t v[IPT];
+    if (full) {
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
-            uint32_t wt;
-            pre[c] = wave_exclusive_scan_small<VBITS>((uint32_t)__popc((flags >> (c * V)) & T::VMASK), wt);
-            if (lane == 0) chunk_tot[c * W + w] = wt;
+        for (int c = 0; c < C; ++c) load_vec<V, true>(in + i0 + c * (kWave * V), &v[c * V]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < IPT; ++k) {
+            const int64_t i = i0 + (k / V) * (kWave * V) + k % V;
+            v[k] = in[i < n ? i : n - 1];
         }
-        __syncthreads();
-        uint32_t cbase[C];
-        uint32_t total = 0;
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-#pragma unroll
-            for (int ww = 0; ww < W; ++ww) {
-                const uint32_t t = chunk_tot[c * W + ww];
-                if (ww == w) cbase[c] = total;
-                total += t;
-            }
-        const uint64_t ob = block_lookback<BLOCK>(st, tile, total, wave_flags, wave_sum);
-        // BlockShuffle: matches to their tile positions in LDS
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            uint32_t pos = cbase[c] + pre[c];
-#pragma unroll
-            for (int e = 0; e < V; ++e)
-                if ((flags >> (c * V + e)) & 1u) buf[pos++] = v[c * V + e];
-        }
-        __syncthreads();
-        if (ob < kPoison)
-            for (uint32_t i = threadIdx.x; i < total; i += BLOCK) __builtin_nontemporal_store(buf[i], out + ob + i);
-        if (tile == n_tiles - 1 && threadIdx.x == 0) *count_out = ob < kPoison ? (int64_t)(ob + total) : -1;
     }
+    uint64_t m[IPT];
+    uint32_t pos[C], run = 0;  // run: the wave's matches so far (uniform)
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        pos[c] = run;
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            const int k = c * V + e;
+            bool q = in_range(v[k], lo, hi);
+            if (!full) q = q && i0 + c * (kWave * V) + e < n;
+            m[k] = ballot(q);
+            pos[c] = __builtin_amdgcn_mbcnt_hi((uint32_t)(m[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[k], pos[c]));
+            run += (uint32_t)__popcll(m[k]);
+        }
+    }
+    if (lane == 0) wave_tot[w] = run;
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        const uint32_t t = wave_tot[i];
+        before = i == w ? total : before;
+        total += t;
+    }
+    if (threadIdx.x == 0) word_store(sums.tile + tile, kPublished | total);
+    // BlockShuffle: matches to their tile positions in LDS
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        uint32_t p = before + pos[c];
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+            const bool q = __builtin_amdgcn_inverse_ballot_w64(m[c * V + e]);
+            if (q) buf[p] = v[c * V + e];
+            p += q ? 1u : 0u;
+        }
+    }
+    // one wave finds the offset, the others wait at the barrier (polling before
+    // the matches are placed, while fewer words are there, costs more than the
+    // wait it saves: 110 us)
+    if (w == W - 1) {
+        const uint64_t ob = matches_before(sums, tile, n_tiles, total);
+        if (lane == 0) out_base = ob;
+    }
+    __syncthreads();
+    const uint64_t ob = out_base;
+    if (ob != ~0ull) store_run<BLOCK>(buf, total, out + ob);
+    // the count was zero: the last tile's total, or -1 from any tile that gave up
+    if (threadIdx.x == 0 && (ob == ~0ull || tile == n_tiles - 1))
+        atomicOr((unsigned long long *)count_out, ob == ~0ull ? ~0ull : ob + total);
 }
 
 // Unstable selection with buffered reservations.  Persistent workgroups
@@ -306,18 +349,7 @@ __global__ __launch_bounds__(BLOCK) void select_buffered_kernel(const int32_t *_
     auto flush = [&]() {
         if (threadIdx.x == 0) flush_off = atomic_add_u64((uint64_t *)count_out, fill);
         __syncthreads();
-        int32_t *dst = out + flush_off;
-        // scalar stores up to a 16-byte boundary, vectors, then the tail
-        uint32_t head = (uint32_t)(((16u - ((uint32_t)(uintptr_t)dst & 15u)) & 15u) >> 2);
-        if (head > fill) head = fill;
-        if (threadIdx.x < head) __builtin_nontemporal_store(buf[threadIdx.x], dst + threadIdx.x);
-        const uint32_t nvec = (fill - head) >> 2;
-        for (uint32_t i = threadIdx.x; i < nvec; i += BLOCK) {
-            const uint32_t b = head + 4 * i;
-            const v4i x = {buf[b], buf[b + 1], buf[b + 2], buf[b + 3]};
-            __builtin_nontemporal_store(x, reinterpret_cast<v4i *>(dst + b));
-        }
-        for (uint32_t i = head + 4 * nvec + threadIdx.x; i < fill; i += BLOCK) __builtin_nontemporal_store(buf[i], dst + i);
+        store_run<BLOCK>(buf, fill, out + flush_off);
         __syncthreads();  // buf and flush_off are reused
         fill = 0;
     };
@@ -384,10 +416,12 @@ static hipError_t select_t(const LaunchCfg &cfg, const int32_t *in, int64_t n, i
     // not resident
     hipError_t e;
     if (stable) {
-        e = fill_u64(st, n_tiles, 0ull, s);
+        const TileSums sums(st, n_tiles);
+        const int64_t words = ((const char *)(sums.tile + n_tiles) - (const char *)st + 7) / 8;  // at most n_tiles
+        e = zero_and_word(st, words, (uint64_t *)count, s);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((select_kernel<BLOCK, IPT>), dim3((unsigned)n_tiles), dim3(BLOCK), 0, s, in, n,
-                           lo, hi, out, st, count, n_tiles);
+                           lo, hi, out, sums, count, n_tiles);
     } else {
         e = fill_u64((uint64_t *)count, 1, 0ull, s);
         if (e != hipSuccess) return e;
@@ -414,7 +448,11 @@ int64_t select_tile_items(const LaunchCfg &cfg) { return (int64_t)cfg.block * cf
 hipError_t launch_select(const LaunchCfg &cfg, const int32_t *in, int64_t n, int32_t lo, int32_t hi,
                          int32_t *out, int64_t *count, uint64_t *status_words, bool stable, hipStream_t s) {
     if (n == 0 || lo > hi) return fill_u64((uint64_t *)count, 1, 0ull, s);
-    switch (CRYSTAL_VARIANT_KEY(cfg.block, cfg.ipt)) {
+    // The stable kernel waits once per tile: the shape tuned for the unordered
+    // one runs with twice the threads (64M rows, half of them qualifying: 512 x
+    // 16 105 us, 1024 x 16 83, 1024 x 32 91; fewer words than 512 x 16 needs).
+    const int block = stable && cfg.block == 512 && cfg.ipt == 16 ? 1024 : cfg.block;
+    switch (CRYSTAL_VARIANT_KEY(block, cfg.ipt)) {
 #define X(B, I) \
     case CRYSTAL_VARIANT_KEY(B, I): return select_t<B, I>(cfg, in, n, lo, hi, out, count, status_words, stable, s);
         CRYSTAL_VARIANTS_ALL(X)

@@ -347,3 +347,33 @@ def test_probe_of_sliced_and_staged_tables(kind, dim, n):
     cx.check_status(ht.build(dev(key), dev(val)))
     assert tuple(ht.probe(dev(fk)).cpu().tolist()) == oracle.join_sum(key, val, fk)
     assert tuple(ht.probe(dev(fk), dev(pv)).cpu().tolist()) == oracle.join_sum(key, val, fk, pval=pv)
+
+
+# ------------------------------------------------ stable selection's sums --
+@pytest.mark.parametrize("tiles", [1, 2, 63, 64, 65, 66, 128, 129, 4095, 4096, 4097, 4160, 8192, 8193, 66 * 4096 + 70])
+@pytest.mark.parametrize("short", [0, 63])
+def test_select_stable_tile_counts(tiles, short):
+    """Tile counts around a group (64 tiles), a supergroup (4,096) and 64
+    supergroups, with a full and a one-item last tile."""
+    announce("select stable tiles", tiles, short)
+    cx.tune_set(cx.K_SELECT, 64, 1, 0)                     # 64-item tiles
+    n = tiles * 64 - short
+    y = datagen.select_column(n, workload=3000 + tiles)
+    for sigma in (0.5, 1.0):
+        lo, hi = datagen.select_threshold_range(sigma)
+        out, cnt = cx.select(dev(y), lo, hi, stable=True)
+        check_select(out, cnt, y, lo, hi, True)
+
+
+@pytest.mark.parametrize("block,ipt", [(64, 1), (64, 2), (128, 4), (512, 16), (1024, 16)])
+def test_select_stable_shares_exact_scratch(block, ipt):
+    """The least scratch, with stale contents, over several tiles per group."""
+    announce("select stable scratch", block, ipt)
+    cx.tune_set(cx.K_SELECT, block, ipt, 0)
+    n = 70 * block * ipt + 1
+    need = cx.load().crystal_select_stable_scratch_bytes(n)
+    guarded = torch.full((need + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+    y = datagen.select_column(n, workload=3100 + ipt)
+    out, cnt = cx.select(dev(y), 0, 2 ** 30, stable=True, scratch=guarded[:need])
+    check_select(out, cnt, y, 0, 2 ** 30, True)
+    assert bool((guarded[need:] == 0xFF).all())
