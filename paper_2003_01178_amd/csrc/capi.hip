@@ -88,6 +88,22 @@ static std::vector<TuneEntry> g_tune;
 
 static constexpr LaunchCfg kRadixLong = {1024, 16, 0};
 
+// Short inputs: small tiles, so that more CUs share them; the sort's four
+// passes, pairs, in us, at this shape and at 1024 x 16: 30,000 37/90, 100,003
+// 45/82, 400,000 53/91, 1M 62/91, 2M 79/99, 10M 231/207 (512 x 8 / 1024 x 16
+// from 2M on).  Long ones: long runs per partition, as long as the lines that
+// an XCD's workgroups have open (256 per workgroup and column) fit its L2: a
+// partition pass over 2^28 pairs 1,373 us at 1024 x 16, 1,213 at 1024 x 8
+// (2^26 333/307, 2^24 80/84), over 2^28 keys 763/924, at 512 x 16 747.
+static LaunchCfg radix_default(int64_t n, bool vals) {
+    if (n <= 1 << 16) return {256, 4, 0};
+    if (n <= 1 << 18) return {512, 4, 0};
+    if (n <= 1 << 20) return {1024, 4, 0};
+    if (n <= 1 << 23) return {512, 8, 0};
+    if (!vals) return {512, 16, 0};
+    return n <= 1 << 25 ? kRadixLong : LaunchCfg{1024, 8, 0};
+}
+
 static LaunchCfg default_cfg(int kernel, int64_t n) {
     switch (kernel) {
     case CRYSTAL_K_SELECT: return {1024, 16, 0};
@@ -97,16 +113,7 @@ static LaunchCfg default_cfg(int kernel, int64_t n) {
     case CRYSTAL_K_STAR: return {256, 16, 0};
     case CRYSTAL_K_SHARED_SCAN: return {1024, 16, 0};
     case CRYSTAL_K_SHARED_SCAN_SCALAR: return {1024, 8, 0};
-    case CRYSTAL_K_RADIX:
-        // Short inputs: small tiles, so that more CUs share them; the sort's
-        // four passes, pairs, in us, at this shape and at 1024 x 16: 30,000
-        // 37/90, 100,003 45/82, 400,000 53/91, 1M 62/91, 2M 79/99, 10M 231/207
-        // (512 x 8 / 1024 x 16 from 2M on).  Long ones: the longest runs.
-        if (n <= 1 << 16) return {256, 4, 0};
-        if (n <= 1 << 18) return {512, 4, 0};
-        if (n <= 1 << 20) return {1024, 4, 0};
-        if (n <= 1 << 23) return {512, 8, 0};
-        return kRadixLong;
+    case CRYSTAL_K_RADIX: return radix_default(n, false);
     default: return {256, 16, 0};
     }
 }
@@ -138,18 +145,17 @@ LaunchCfg radix_long_cfg(int64_t n) {
     return tuned(CRYSTAL_K_RADIX, n, c) ? c : kRadixLong;
 }
 
-// Scratch of a partition pass: what is asked for, and the least accepted.
-static int64_t radix_scratch_least(int64_t n) { return radix_pass_min_scratch_bytes(radix_long_cfg(n), n); }
-static int64_t radix_scratch_bytes(int64_t n) {
-    const int64_t best = radix_pass_scratch_bytes(tune_lookup(CRYSTAL_K_RADIX, n), n), least = radix_scratch_least(n);
-    return best > least ? best : least;
+LaunchCfg radix_cfg(int64_t n, bool vals, int64_t scratch_bytes) {
+    LaunchCfg c;
+    if (!tuned(CRYSTAL_K_RADIX, n, c)) c = radix_default(n, vals);
+    return scratch_bytes < radix_pass_scratch_bytes(c, n) ? radix_long_cfg(n) : c;
 }
 
-// Shape of a partition pass with so much scratch: smaller tiles need more of
-// it, and a call that brings only the least runs with the long shape.
-static LaunchCfg radix_cfg(int64_t n, int64_t scratch_bytes) {
-    const LaunchCfg c = tune_lookup(CRYSTAL_K_RADIX, n);
-    return scratch_bytes < radix_pass_scratch_bytes(c, n) ? radix_long_cfg(n) : c;
+// Scratch of a partition pass: what is asked for, and the least accepted.
+static int64_t radix_scratch_least(int64_t n) { return radix_pass_min_scratch_bytes(radix_long_cfg(n), n); }
+static int64_t radix_scratch_bytes(int64_t n, bool vals) {
+    const int64_t best = radix_pass_scratch_bytes(radix_cfg(n, vals, INT64_MAX), n), least = radix_scratch_least(n);
+    return best > least ? best : least;
 }
 
 static bool variant_exists(int kernel, int block, int ipt) {
@@ -704,7 +710,8 @@ crystal_status crystal_radix_histogram(const uint32_t *keys, int64_t n, int32_t 
 }
 
 size_t crystal_radix_partition_scratch_bytes(int64_t n) {
-    return (size_t)radix_scratch_bytes(n);
+    const int64_t keys = radix_scratch_bytes(n, false), pairs = radix_scratch_bytes(n, true);
+    return (size_t)(keys > pairs ? keys : pairs);
 }
 
 static crystal_status radix_partition_common(const uint32_t *keys, const uint32_t *vals, int64_t n, int32_t shift,
@@ -713,7 +720,7 @@ static crystal_status radix_partition_common(const uint32_t *keys, const uint32_
                                              void *stream, bool stable) {
     if (bits < 1 || bits > 8 || shift < 0 || shift + bits > 32 || !radix_args_ok(keys, vals, n, out_keys, out_vals))
         return CRYSTAL_EINVAL;
-    const LaunchCfg cfg = radix_cfg(n, (int64_t)scratch_bytes);
+    const LaunchCfg cfg = radix_cfg(n, vals != nullptr, (int64_t)scratch_bytes);
     if (!radix_variant_fits(cfg.block, cfg.ipt)) return CRYSTAL_EINVAL;
     if (n > 0) {
         if (!scratch || ((uintptr_t)scratch & 255u)) return scratch ? CRYSTAL_EINVAL : CRYSTAL_ESCRATCH;
@@ -744,7 +751,7 @@ static int64_t round256(int64_t b) { return (b + 255) / 256 * 256; }
 size_t crystal_sort_pairs_scratch_bytes(int64_t n, int32_t with_values) {
     if (n <= 0) return 256;
     const int64_t copy = round256(n * 4);
-    return (size_t)(copy * (with_values ? 2 : 1) + radix_scratch_bytes(n));
+    return (size_t)(copy * (with_values ? 2 : 1) + radix_scratch_bytes(n, with_values != 0));
 }
 
 // Four stable 8-bit passes from the low byte up, in -> tmp -> out -> tmp ->
@@ -770,7 +777,7 @@ crystal_status crystal_sort_pairs(const uint32_t *keys, const uint32_t *vals, in
     if (n == 0) return CRYSTAL_OK;
     const int64_t copy = round256(n * 4);
     const int64_t pass_bytes = (int64_t)scratch_bytes - copy * (vals ? 2 : 1);
-    const LaunchCfg cfg = radix_cfg(n, pass_bytes);
+    const LaunchCfg cfg = radix_cfg(n, vals != nullptr, pass_bytes);
     if (!radix_variant_fits(cfg.block, cfg.ipt)) return CRYSTAL_EINVAL;
     if (!scratch || ((uintptr_t)scratch & 255u)) return scratch ? CRYSTAL_EINVAL : CRYSTAL_ESCRATCH;
     if (pass_bytes < radix_scratch_least(n)) return CRYSTAL_ESCRATCH;
@@ -807,7 +814,7 @@ crystal_status crystal_sort_pairs_msb(const uint32_t *keys, const uint32_t *vals
         const int64_t pass_bytes = (int64_t)scratch_bytes - copy * (vals ? 2 : 1);
         uint32_t *tk = (uint32_t *)scratch;
         uint32_t *tv = vals ? (uint32_t *)((char *)scratch + copy) : nullptr;
-        return sort_lsb(radix_cfg(n, pass_bytes), keys, vals, n, out_keys, out_vals, tk, tv,
+        return sort_lsb(radix_cfg(n, vals != nullptr, pass_bytes), keys, vals, n, out_keys, out_vals, tk, tv,
                         (char *)scratch + copy * (vals ? 2 : 1), pass_bytes, stream);
     }
     return from_hip(launch_msb_sort(keys, vals, n, out_keys, out_vals, scratch, as_stream(stream)));

@@ -35,8 +35,11 @@ inline int64_t grid_for(int64_t n_tiles, const LaunchCfg &cfg) {
 }
 
 LaunchCfg tune_lookup(int kernel, int64_t n);
-// Radix shape for a partition of many tiles per CU: the tuned one, else 1024 x 16.
+// Radix shapes: the tuned one, else 1024 x 16; and of a partition pass with so
+// much scratch, the tuned one, else by the size and whether there are values,
+// or the former when that shape's counts do not fit.
 LaunchCfg radix_long_cfg(int64_t n);
+LaunchCfg radix_cfg(int64_t n, bool vals, int64_t scratch_bytes);
 
 inline crystal_status from_hip(hipError_t e) {
     return e == hipSuccess ? CRYSTAL_OK : CRYSTAL_EHIP;

@@ -37,8 +37,9 @@ namespace {
 
 constexpr uint32_t kLocalMax = 8192;  // pairs one local-sort workgroup holds (512 threads x 16)
 constexpr uint32_t kSmallSeg = 1024;  // sub-segments shorter than this are grouped into one task
-constexpr int kPartBlock = 1024, kPartIpt = 16;
-constexpr uint32_t kChunk = kPartBlock * kPartIpt;  // pairs per partition chunk: one tile
+constexpr int kPartBlock = 1024;
+constexpr int kPartIpt = 16;
+constexpr uint32_t kChunk = kPartBlock * kPartIpt;    // pairs per partition chunk: one tile
 constexpr uint32_t kCopy = 65536;     // pairs per copy task
 constexpr int kLocBlock = 512, kLocIpt = 16;  // tasks up to kLocalMax pairs
 constexpr int kSmlBlock = 256, kSmlIpt = 17;  // tasks up to kSmallMax pairs, eight workgroups per CU
@@ -252,19 +253,35 @@ __device__ __forceinline__ void plan_segment(Ctl *ctl, int cur, const uint32_t *
         __syncthreads();
         return;
     }
-    __shared__ uint32_t count[3];
-    if (d < 3) count[d] = 0u;
-    __syncthreads();
-    // 2: a big segment of the next level; 0, 1: a task of that list; 3: nothing
+    // 2: a big segment of the next level; 0, 1: a task of that list; 3: nothing.
+    // Entries keep the digits' order, so that neighbours are sorted at about the
+    // same time.
+    constexpr int W = kAuxBlock / kWave;
+    __shared__ uint32_t count[3][W];
     const int kind = len == 0 ? 3 : len > kLocalMax ? 2 : task_list(len, (uint32_t)shift);
     uint32_t at = 0;
-    if (kind < 3) at = atomicAdd(&count[kind], 1u);
-    __syncthreads();
-    if (d == 0) {
-        base_big = count[2] ? atomicAdd(&ctl->n_big[cur ^ 1], count[2]) : 0u;
-        for (int l = 0; l < 2; ++l) base_task[l] = count[l] ? atomicAdd(&ctl->n_tasks[l], count[l]) : 0u;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const uint64_t m = ballot(kind == k);
+        if (kind == k) at = count_below(m);
+        if (lane_id() == 0) count[k][d / kWave] = (uint32_t)__popcll(m);
     }
     __syncthreads();
+    if (d < 3) {
+        uint32_t total = 0;
+        for (int w = 0; w < W; ++w) {
+            const uint32_t c = count[d][w];
+            count[d][w] = total;
+            total += c;
+        }
+        const uint32_t base = total ? atomicAdd(d == 2 ? &ctl->n_big[cur ^ 1] : &ctl->n_tasks[d], total) : 0u;
+        if (d == 2)
+            base_big = base;
+        else
+            base_task[d] = base;
+    }
+    __syncthreads();
+    if (kind < 3) at += count[kind][d / kWave];
     if (kind == 2)
         next[base_big + at] = Seg{st[d], len, 0u, 0u};
     else if (kind < 2)
@@ -406,8 +423,7 @@ __global__ __launch_bounds__(BLOCK, 8) void msb_local_kernel(const Ctl *ctl, int
         uint32_t key[IPT], val[IPT];
         load_tile<BLOCK, IPT, false>(src_k(task) + task.start, 0, len, off0, key);
         if (VALS) load_tile<BLOCK, IPT, false>(src_v(task) + task.start, 0, len, off0, val);
-        sort_in_lds<BLOCK, IPT, VALS>(key, val, len, task.bits, out_k + task.start,
-                                      VALS ? out_v + task.start : nullptr, lds);
+        sort_in_lds<BLOCK, IPT, VALS>(key, val, len, task.bits, out_k, out_v, task.start, lds);
     }
 }
 
@@ -422,7 +438,7 @@ __global__ __launch_bounds__(BLOCK) void sort_short_kernel(const uint32_t *__res
     uint32_t key[IPT], val[IPT];
     load_tile<BLOCK, IPT, false>(in_k, 0, n, RT::offset(0), key);
     if (VALS) load_tile<BLOCK, IPT, false>(in_v, 0, n, RT::offset(0), val);
-    sort_in_lds<BLOCK, IPT, VALS>(key, val, n, 32u, out_k, out_v, lds);
+    sort_in_lds<BLOCK, IPT, VALS>(key, val, n, 32u, out_k, out_v, 0u, lds);
 }
 
 template <bool VALS>
@@ -531,12 +547,13 @@ hipError_t msb_run(const uint32_t *keys, const uint32_t *vals, int64_t n, uint32
     // level 0: the whole input is one segment, so the plain stable partition
     // pass on the top byte does it (input -> output), and its partition
     // offsets give the first level's sub-segments
-    const LaunchCfg rcfg = radix_long_cfg(n);
-    // its count matrix goes where the later levels' counts will be, if it fits there
-    const bool in_hist = L.max_chunks * kBins * 4 >= radix_pass_scratch_bytes(rcfg, n);
+    const int64_t hist_bytes = L.max_chunks * kBins * 4;
+    const LaunchCfg rcfg = radix_cfg(n, VALS, hist_bytes);
+    // its counts go where the later levels' will be, if they fit there
+    const bool in_hist = hist_bytes >= radix_pass_scratch_bytes(rcfg, n);
     e = launch_radix_partition(rcfg, keys, vals, n, 24, 8, ok, ov, (uint32_t *)(base + L.part),
-                               in_hist ? base + L.hist : base + L.pass,
-                               in_hist ? L.max_chunks * kBins * 4 : L.total - L.pass, true, s);
+                               in_hist ? base + L.hist : base + L.pass, in_hist ? hist_bytes : L.total - L.pass, true,
+                               s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(msb_level0_kernel, dim3(1), dim3(kAuxBlock), 0, s, ctl, (const uint32_t *)(base + L.part),
                        (uint32_t)n, big[1], tasks, stride);

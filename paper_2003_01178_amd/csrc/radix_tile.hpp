@@ -261,13 +261,15 @@ __device__ __forceinline__ void shuffle_range(const uint32_t *__restrict__ keys,
         // 4. out, consecutive lanes to consecutive places of a partition
         int tidv = tid;  // opaque: keeps per-item offsets out of registers
         asm volatile("" : "+v"(tidv));
-        uint32_t g[IPT];
+        uint32_t digits[(IPT + 3) / 4];  // of the items written, four per word, for the values
 #pragma unroll
         for (int j = 0; j < IPT; ++j) {
             const int p = j * BLOCK + tidv;
             const uint32_t k = stage[p];
-            g[j] = s_gbase[digit_of(k, shift, mask)] + (uint32_t)p;  // < n < 2^32
-            if (p < rem) out_keys[g[j]] = k;
+            const uint32_t d = digit_of(k, shift, mask);
+            if (VALS) digits[j / 4] = j % 4 ? digits[j / 4] | d << (j % 4 * 8) : d;
+            const uint32_t g = s_gbase[d] + (uint32_t)p;  // < n < 2^32
+            if (p < rem) out_keys[g] = k;
             if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (VALS) {
@@ -283,7 +285,8 @@ __device__ __forceinline__ void shuffle_range(const uint32_t *__restrict__ keys,
 #pragma unroll
             for (int j = 0; j < IPT; ++j) {
                 const int p = j * BLOCK + tidv;
-                if (p < rem) out_vals[g[j]] = stage[p];
+                const uint32_t g = s_gbase[(digits[j / 4] >> (j % 4 * 8)) & 0xffu] + (uint32_t)p;
+                if (p < rem) out_vals[g] = stage[p];
                 if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -293,10 +296,12 @@ __device__ __forceinline__ void shuffle_range(const uint32_t *__restrict__ keys,
 }
 
 // Sort of a tile: the items key (and val), `len` of them in tile layout, by
-// their low `bits` key bits with stable 8-bit passes, written to out_k (out_v).
+// their low `bits` key bits with stable 8-bit passes, written to out_k (out_v)
+// from `start` on.  (With the sum of the two as a restrict pointer the MSB sort's
+// local passes took 1,490 us instead of 1,250.)
 template <int BLOCK, int IPT, bool VALS>
 __device__ __forceinline__ void sort_in_lds(uint32_t (&key)[IPT], uint32_t (&val)[IPT], int len, uint32_t bits,
-                                            uint32_t *__restrict__ out_k, uint32_t *__restrict__ out_v,
+                                            uint32_t *out_k, uint32_t *out_v, uint32_t start,
                                             uint32_t *lds) {
     using RT = RadixTile<BLOCK, IPT>;
     uint32_t *stage = lds + RT::STAGE;
@@ -326,7 +331,7 @@ __device__ __forceinline__ void sort_in_lds(uint32_t (&key)[IPT], uint32_t (&val
         __syncthreads();
         const bool last = sh + 8 >= bits;
         if (last) {
-            for (int i = tid; i < len; i += BLOCK) out_k[i] = stage[i];
+            for (int i = tid; i < len; i += BLOCK) out_k[start + i] = stage[i];
         } else {
 #pragma unroll
             for (int k = 0; k < IPT; ++k) key[k] = stage[off0 + k * kWave];
@@ -337,7 +342,7 @@ __device__ __forceinline__ void sort_in_lds(uint32_t (&key)[IPT], uint32_t (&val
             for (int k = 0; k < IPT; ++k) stage[pos.get(k)] = val[k];
             __syncthreads();
             if (last) {
-                for (int i = tid; i < len; i += BLOCK) out_v[i] = stage[i];
+                for (int i = tid; i < len; i += BLOCK) out_v[start + i] = stage[i];
             } else {
 #pragma unroll
                 for (int k = 0; k < IPT; ++k) val[k] = stage[off0 + k * kWave];
