@@ -803,13 +803,13 @@ crystal_status crystal_sort_pairs_msb(const uint32_t *keys, const uint32_t *vals
     const LaunchCfg cfg = radix_long_cfg(n);  // the first level's partition pass
     if (!radix_variant_fits(cfg.block, cfg.ipt)) return CRYSTAL_EINVAL;
     if (n <= kSortShortMax) return from_hip(launch_sort_short(keys, vals, n, out_keys, out_vals, as_stream(stream)));
-    // Below 2^25 pairs four passes from the low byte up, which give the same
+    // Up to 2^27 pairs four passes from the low byte up, which give the same
     // order, are faster than the levels, and do not depend on the keys (pairs,
-    // in us, passes / levels: 100,003 45/172, 1M 63/84, 10M 217/280, 33M
-    // 565/647, 60M 1,116/1,078; 20-bit keys 33M 634/924).  A tuned shape keeps
+    // in us, passes / levels: 100,003 45/172, 1M 63/84, 10M 226/280, 45M
+    // 782/808, 134M 2,328/2,356; 20-bit keys 134M 2,581/4,469).  A tuned shape keeps
     // the levels.
     LaunchCfg set;
-    if (n <= int64_t(1) << 25 && !tuned(CRYSTAL_K_RADIX, n, set)) {
+    if (n <= int64_t(1) << 27 && !tuned(CRYSTAL_K_RADIX, n, set)) {
         const int64_t copy = round256(n * 4);
         const int64_t pass_bytes = (int64_t)scratch_bytes - copy * (vals ? 2 : 1);
         uint32_t *tk = (uint32_t *)scratch;

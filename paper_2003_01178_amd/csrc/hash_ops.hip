@@ -2,6 +2,7 @@
 // and the dense group-by aggregate.
 #include "block.hpp"
 #include "internal.hpp"
+#include "stage.hpp"
 #include "variants.hpp"
 
 namespace crystal {

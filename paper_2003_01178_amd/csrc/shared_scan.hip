@@ -22,6 +22,7 @@
 // can be answered over several launches that cover successive row ranges.
 #include "block.hpp"
 #include "internal.hpp"
+#include "stage.hpp"
 #include "variants.hpp"
 
 namespace crystal {
@@ -426,6 +427,12 @@ __global__ __launch_bounds__(BLOCK) void shared_scan_kernel(const BatchDev batch
             m = step_one(b, lds_words, s, x, m);
         }
         if (m == 0u) return;
+        // the measures and the group joins' keys together, then their payloads
+        int32_t fk[CRYSTAL_MAX_JOINS], pay[CRYSTAL_MAX_JOINS];
+        const bool grouped = !p.scalar;
+#pragma unroll
+        for (int jj = 0; jj < CRYSTAL_MAX_JOINS; ++jj)
+            if (grouped && jj < p.n_joins && p.joins[jj].g_bits != 0) fk[jj] = p.col[p.joins[jj].fk_col].p[row];
         uint64_t val = 1;
         if (p.agg != CRYSTAL_AGG_COUNT) {
             const int64_t a = p.col[p.agg_col0].p[row];
@@ -434,19 +441,25 @@ __global__ __launch_bounds__(BLOCK) void shared_scan_kernel(const BatchDev batch
             val = (uint64_t)(p.agg == CRYSTAL_AGG_SUM ? a : p.agg == CRYSTAL_AGG_SUM_PRODUCT ? a * c : a - c);
         }
         int64_t g = 0;
-        if (!p.scalar) {
-            for (int jj = 0; jj < p.n_joins; ++jj) {
+        if (grouped) {
+#pragma unroll
+            for (int jj = 0; jj < CRYSTAL_MAX_JOINS; ++jj) {
                 const StarJoinDev &j = p.joins[jj];
-                if (j.g_bits == 0) continue;
-                const int32_t fk = p.col[j.fk_col].p[row];
-                int32_t pay = 0;
+                if (jj >= p.n_joins || j.g_bits == 0) continue;
+                pay[jj] = 0;
                 if (j.kind == CRYSTAL_HT_DIRECT) {
-                    const uint32_t off = (uint32_t)fk - (uint32_t)j.key_min;
-                    if ((int64_t)off < j.span && j.payload) pay = j.payload[off];
-                } else if (fk != kEmptyKey) {
-                    probe_linear((const v2i *)j.slots, j.mask, j.shift, fk, pay);
+                    const uint32_t off = (uint32_t)fk[jj] - (uint32_t)j.key_min;
+                    if ((int64_t)off < j.span && j.payload) pay[jj] = j.payload[off];
+                } else if (fk[jj] != kEmptyKey) {
+                    probe_linear((const v2i *)j.slots, j.mask, j.shift, fk[jj], pay[jj]);
                 }
-                g += ((int64_t)payload_field(pay, j.g_shift, j.g_mask, j.g_bits) - (int64_t)j.g_base) * j.g_stride;
+            }
+#pragma unroll
+            for (int jj = 0; jj < CRYSTAL_MAX_JOINS; ++jj) {
+                const StarJoinDev &j = p.joins[jj];
+                if (jj < p.n_joins && j.g_bits != 0)
+                    g += ((int64_t)payload_field(pay[jj], j.g_shift, j.g_mask, j.g_bits) - (int64_t)j.g_base) *
+                         j.g_stride;
             }
             if ((uint64_t)g >= (uint64_t)p.n_groups) {
                 bad_group = true;
