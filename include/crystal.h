@@ -579,8 +579,9 @@ crystal_status crystal_radix_histogram(const uint32_t *keys, int64_t n, int32_t 
                                        uint32_t *hist, void *stream);
 
 /* Scratch (device, 256-byte aligned) of one partition pass over n keys     */
-/* with the current tuning: the per-workgroup digit counts and their        */
-/* prefix sums.                                                             */
+/* with the current tuning: the digit counts of every tile and their prefix */
+/* sums.  A call accepts less, down to the counts of a few workgroups per   */
+/* compute unit, and is slower with it.                                     */
 size_t crystal_radix_partition_scratch_bytes(int64_t n);
 
 /* One partition pass: histogram + shuffle.  Writes the pairs into 2^bits   */
@@ -620,6 +621,8 @@ crystal_status crystal_sort_pairs(const uint32_t *keys, const uint32_t *vals, in
 /* (the first level splits the whole input by the top byte); every shorter  */
 /* segment is then sorted in LDS by its remaining low bits by one           */
 /* workgroup.  Uniform keys take two partition levels and the local pass.   */
+/* Up to 2^27 pairs, where four passes from the low byte up are as fast, it */
+/* takes those unless a radix shape is tuned.                               */
 /* Arguments, ownership and errors as crystal_sort_pairs; scratch (device,  */
 /* 256-byte aligned) of crystal_sort_pairs_msb_scratch_bytes(n, with_values) */
 /* bytes holds one copy of the pairs and the work lists.                    */

@@ -113,7 +113,7 @@ static LaunchCfg default_cfg(int kernel, int64_t n) {
     case CRYSTAL_K_STAR: return {256, 16, 0};
     case CRYSTAL_K_SHARED_SCAN: return {1024, 16, 0};
     case CRYSTAL_K_SHARED_SCAN_SCALAR: return {1024, 8, 0};
-    case CRYSTAL_K_RADIX: return radix_default(n, false);
+    case CRYSTAL_K_RADIX: return radix_default(n, true);  // of pairs
     default: return {256, 16, 0};
     }
 }

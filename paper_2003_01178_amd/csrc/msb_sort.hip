@@ -26,8 +26,6 @@
 //
 // All work lists live in device memory and every kernel loops over its list
 // (persistent workgroups), so the host never waits for the device.
-#include <type_traits>
-
 #include "block.hpp"
 #include "internal.hpp"
 #include "radix_tile.hpp"

@@ -29,10 +29,9 @@ namespace crystal {
 namespace {
 
 // Exclusive prefix of x over threads 0 .. BLOCK-1 in thread order; `tmp` holds
-// one word per wave.  Every thread calls it.  With TRAIL it ends with a
-// barrier, after which tmp may be reused; without, the caller must pass a
-// barrier before tmp is written again.
-template <int BLOCK, bool TRAIL = true>
+// one word per wave.  Every thread calls it; it ends with a barrier, after
+// which tmp may be reused.
+template <int BLOCK>
 __device__ __forceinline__ uint32_t block_exclusive_scan_u32(uint32_t x, uint32_t *tmp, uint32_t &total) {
     constexpr int W = BLOCK / kWave;
     const uint32_t inc = wave_inclusive_scan(x);
@@ -47,7 +46,7 @@ __device__ __forceinline__ uint32_t block_exclusive_scan_u32(uint32_t x, uint32_
         tot += t;
     }
     total = tot;
-    if (TRAIL) __syncthreads();
+    __syncthreads();
     return before + inc - x;
 }
 
