@@ -135,11 +135,12 @@ __device__ __forceinline__ void scan_counters(uint16_t *wc, uint32_t (&start)[4]
 }
 
 // One column of the tile at `base`, rem items of it.  Places past the end get
-// all ones: the largest digit in every pass and last in input order, so they
-// are ranked like any item and end up behind the others, and only loads and
-// stores test for the end.  The tile's base pointer is made an opaque scalar,
-// so that every load is one scalar base plus one lane offset (global address
-// space: a generic pointer would give flat loads).
+// all ones: the largest digit in every pass and last in input order, so the
+// stable ranking treats them like any item and they end up behind the others;
+// only loads and stores test for the end.  The tile's base
+// pointer is made an opaque scalar, so that every load is one scalar base plus
+// one lane offset (global address space: a generic pointer would give flat
+// loads).
 template <int BLOCK, int IPT, bool NT>
 __device__ __forceinline__ void load_tile(const uint32_t *__restrict__ col, int64_t base, int rem, int off0,
                                           uint32_t (&v)[IPT]) {
@@ -199,8 +200,9 @@ __device__ __forceinline__ void place_keys(const uint32_t (&key)[IPT], int shift
 
 // Items [begin, end) of a column, a tile at a time, to their output places;
 // s_run (RUN) holds each digit's next output offset, complete before the call
-// (the caller's barrier).  !STABLE: ranks from LDS atomics on the wave's
-// counters, which order equal digits of one load arbitrarily.
+// (the caller's barrier).  !STABLE: ranks of a full tile from LDS atomics on
+// the wave's counters, which order equal digits of one load arbitrarily; a
+// partial tile is ranked stably, so that its places past the end come last.
 template <int BLOCK, int IPT, bool VALS, bool STABLE>
 __device__ __forceinline__ void shuffle_range(const uint32_t *__restrict__ keys, const uint32_t *__restrict__ vals,
                                               int64_t begin, int64_t end, int shift, uint32_t mask,
@@ -225,7 +227,7 @@ __device__ __forceinline__ void shuffle_range(const uint32_t *__restrict__ keys,
         //    scatter barrier.
         clear_counters(my_wc);
         __builtin_amdgcn_wave_barrier();
-        if constexpr (STABLE) {
+        if (STABLE || rem < RT::ITEMS) {
 #pragma unroll
             for (int k = 0; k < IPT; ++k) {
                 pos.init(k, stable_rank(digit_of(key[k], shift, mask), my_wc));

@@ -403,3 +403,15 @@ def test_msb_levels_with_a_tuned_shape(n, key_bits):
     assert np.array_equal(u32(ok, n), wk) and np.array_equal(u32(ov, n), wv)
     ok, _ = cx.sort_pairs(dev(k.view(np.int32)), msb=True)
     assert np.array_equal(u32(ok, n), wk)
+
+
+# ------------------------------------------------ partial tiles, unstable --
+@pytest.mark.parametrize("n", [1, 63, 65, 1000, 16_385, 70_003, 1_000_001])
+def test_unstable_partition_of_the_largest_digit_in_a_partial_tile(n):
+    """Every item of the last, partial tile has the largest digit, as the
+    places past its end do; the values are distinct."""
+    announce("radix unstable partial", n)
+    k = np.full(n, 0xFFFFFFFF, dtype=np.uint32)
+    k[:n // 2] = np.random.default_rng(n).integers(0, 1 << 32, size=n // 2, dtype=np.uint64).astype(np.uint32)
+    for shift, bits in ((24, 8), (31, 1)):
+        check_unstable(k, np.arange(n, dtype=np.uint32), shift, bits)
