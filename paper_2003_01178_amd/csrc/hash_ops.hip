@@ -808,7 +808,7 @@ __global__ __launch_bounds__(BLOCK) void groupby_kernel(const int32_t *__restric
                                                         uint64_t *__restrict__ sums,
                                                         int32_t *status, int64_t n_tiles) {
     using T = TileShape<BLOCK, IPT>;
-    extern __shared__ uint64_t part[];
+    extern __shared__ __align__(16) uint64_t part[];
     if constexpr (LDS_PART) {
         for (int64_t i = threadIdx.x; i < n_groups; i += BLOCK) part[i] = 0;
         __syncthreads();

@@ -362,7 +362,7 @@ __global__ __launch_bounds__(kPartBlock, 8) void msb_shuffle_kernel(Ctl *ctl, co
                                                                     uint32_t *__restrict__ ok,
                                                                     uint32_t *__restrict__ ov, int shift) {
     using RT = RadixTile<kPartBlock, kPartIpt>;
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __align__(16) uint32_t lds[];
     uint32_t *s_run = lds + RT::RUN;
     // the chunks of an XCD's workgroups are consecutive (see xcd_item; the grid
     // is a multiple of 8) and are taken in order, so that neighbours are written
@@ -397,7 +397,7 @@ __global__ __launch_bounds__(BLOCK, 8) void msb_local_kernel(const Ctl *ctl, int
                                                              const uint32_t *__restrict__ tmp_k,
                                                              const uint32_t *__restrict__ tmp_v) {
     using RT = RadixTile<BLOCK, IPT>;
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __align__(16) uint32_t lds[];
     const int tid = threadIdx.x;
     const int off0 = RT::offset(0);
     const uint32_t nt = ctl->n_tasks[list];

@@ -192,7 +192,7 @@ __global__ __launch_bounds__(BLOCK, 8) void radix_shuffle_kernel(
     const uint32_t *__restrict__ totals, uint32_t *__restrict__ out_keys, uint32_t *__restrict__ out_vals,
     uint32_t *__restrict__ part_offsets) {
     using RT = RadixTile<BLOCK, IPT>;
-    extern __shared__ uint32_t lds[];
+    extern __shared__ __align__(16) uint32_t lds[];
     uint32_t *s_run = lds + RT::RUN;
     const int tid = threadIdx.x;
     const int64_t block = xcd_item(blockIdx.x, gridDim.x);

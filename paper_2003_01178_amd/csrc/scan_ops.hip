@@ -339,7 +339,7 @@ __global__ __launch_bounds__(BLOCK) void select_buffered_kernel(const int32_t *_
     using T = TileShape<BLOCK, IPT>;
     constexpr int W = T::WAVES;
     constexpr uint32_t CAP = 2 * T::ITEMS;
-    extern __shared__ int32_t buf[];  // CAP entries, then one spare word per thread
+    extern __shared__ __align__(16) int32_t buf[];  // CAP entries, then one spare word per thread
     __shared__ uint32_t wave_tot[W];
     __shared__ uint64_t flush_off;
     const int w = threadIdx.x / kWave;

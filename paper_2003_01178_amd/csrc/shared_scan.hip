@@ -297,7 +297,7 @@ __global__ __launch_bounds__(BLOCK) void shared_scan_kernel(const BatchDev batch
     // reduced once per workgroup at the end.
     // dynamic LDS: b.n_queries * 64 64-bit slots for a scalar plan, then the
     // staged mask tables (see MaskDev::stage_off)
-    extern __shared__ uint64_t dyn[];
+    extern __shared__ __align__(16) uint64_t dyn[];
     uint64_t(*acc)[kWave] = reinterpret_cast<uint64_t(*)[kWave]>(dyn);
     uint32_t *lds_words = reinterpret_cast<uint32_t *>(dyn);
     const uint32_t lane = threadIdx.x & (kWave - 1);
