@@ -705,7 +705,11 @@ crystal_status crystal_radix_histogram(const uint32_t *keys, int64_t n, int32_t 
     if (bits < 1 || bits > 8 || shift < 0 || shift + bits > 32 || !hist || n < 0 || n > (int64_t)UINT32_MAX - 1 ||
         (n > 0 && (!keys || ((uintptr_t)keys & 3u))))
         return CRYSTAL_EINVAL;
-    const LaunchCfg cfg = tune_lookup(CRYSTAL_K_RADIX, n);
+    // Long tiles from 2^17 keys on: a workgroup ends with an atomic per digit on
+    // the few lines of `hist`, where adds serialise (2^20 keys at the pairs'
+    // shape / at 1024 x 16, in us: 9.6/7.1, 2^22 24.1/10.9, 2^23 43.5/16.1; the
+    // other way round 30,000 5.5/6.5, 100,003 6.1/6.2).
+    const LaunchCfg cfg = n <= 1 << 17 ? tune_lookup(CRYSTAL_K_RADIX, n) : radix_long_cfg(n);
     return from_hip(launch_radix_histogram(cfg, keys, n, shift, bits, hist, as_stream(stream)));
 }
 

@@ -415,3 +415,26 @@ def test_unstable_partition_of_the_largest_digit_in_a_partial_tile(n):
     k[:n // 2] = np.random.default_rng(n).integers(0, 1 << 32, size=n // 2, dtype=np.uint64).astype(np.uint32)
     for shift, bits in ((24, 8), (31, 1)):
         check_unstable(k, np.arange(n, dtype=np.uint32), shift, bits)
+
+
+# --------------------------------------------------- times of one call against another's --
+def graph_us(launch):
+    from paper_2003_01178_amd import autotune
+    return min(autotune.time_graph_ms(launch) for _ in range(3)) * 1e3
+
+
+def histogram_us(n):
+    k = torch.randint(-(1 << 31), 1 << 31, (n,), device="cuda", dtype=torch.int32)
+    h = torch.zeros(256, dtype=torch.int32, device="cuda")
+    return graph_us(lambda s: cx._check(cx.load().crystal_radix_histogram(cx._ptr(k), n, 8, 8, cx._ptr(h),
+                                                                          cx._stream(s)), "histogram"))
+
+
+def test_histogram_time_grows_with_the_input():
+    """A histogram's workgroups all add to the same few lines, so their number
+    must not follow the small tiles of the partition: 2^22 and 2^23 keys take
+    no longer than 10^7 (by a quarter, for noise)."""
+    announce("radix histogram times")
+    most = 1.25 * histogram_us(10_000_000)
+    for n in (1 << 20, 1 << 22, 1 << 23):
+        assert histogram_us(n) <= most, n
