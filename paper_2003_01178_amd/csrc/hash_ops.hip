@@ -296,32 +296,15 @@ struct ProbeRegs {
 // and 2^10 from 235 to 94 (the keys' own 512 MB take 83).  PP: probe rows carry a payload
 // (pp is not null), a separate instance so that the payload registers exist
 // only when used.
+//
+// probe_tiles: every gridDim.x-th tile from the workgroup's own on, added to sum
+// and cnt.  slots: the linear table; lds_words: what of a direct table is staged.
 template <int BLOCK, int IPT, int MODE, bool PP>
-__global__ __launch_bounds__(BLOCK) void ht_probe_kernel(DevTable t, const int32_t *__restrict__ fk,
-                                                         const int32_t *__restrict__ pp, int64_t n,
-                                                         uint64_t *__restrict__ out_sum,
-                                                         uint64_t *__restrict__ out_cnt,
-                                                         int64_t n_tiles) {
+__device__ __forceinline__ void probe_tiles(const DevTable &t, const v2i *slots, const uint32_t *lds_words,
+                                            const int32_t *__restrict__ fk, const int32_t *__restrict__ pp, int64_t n,
+                                            int64_t n_tiles, uint64_t &sum, uint64_t &cnt) {
     using T = TileShape<BLOCK, IPT>;
-    extern __shared__ v4i lds_raw[];
-    __shared__ uint64_t red[T::WAVES];
-    const v2i *slots = t.slots;
-    if constexpr (MODE == 1) {
-        // stage the whole table
-        copy_to_lds<BLOCK>(reinterpret_cast<const uint32_t *>(t.slots), reinterpret_cast<uint32_t *>(lds_raw),
-                           2 * ((int)t.mask + 1));
-        __syncthreads();
-        slots = reinterpret_cast<const v2i *>(lds_raw);
-    }
-    const uint32_t *lds_words = reinterpret_cast<const uint32_t *>(lds_raw);
     const int bitmap_words = (int)direct_bitmap_words(t.span);
-    if constexpr (MODE == 3 || MODE == 4) {
-        // stage the bitmap, and the payloads, which follow it in memory
-        copy_to_lds<BLOCK>(t.bitmap, reinterpret_cast<uint32_t *>(lds_raw),
-                           bitmap_words + (MODE == 4 ? (int)t.span : 0));
-        __syncthreads();
-    }
-    uint64_t sum = 0, cnt = 0;
     // one tile: the probes of its (already loaded) keys
     auto probe_tile = [&](int64_t tile, const ProbeRegs<IPT, PP> &r) {
         const int32_t(&key)[IPT] = r.key;
@@ -464,6 +447,35 @@ __global__ __launch_bounds__(BLOCK) void ht_probe_kernel(DevTable t, const int32
         tile = nxt;
     }
     }
+}
+
+template <int BLOCK, int IPT, int MODE, bool PP>
+__global__ __launch_bounds__(BLOCK) void ht_probe_kernel(DevTable t, const int32_t *__restrict__ fk,
+                                                         const int32_t *__restrict__ pp, int64_t n,
+                                                         uint64_t *__restrict__ out_sum,
+                                                         uint64_t *__restrict__ out_cnt,
+                                                         int64_t n_tiles) {
+    using T = TileShape<BLOCK, IPT>;
+    extern __shared__ v4i lds_raw[];
+    __shared__ uint64_t red[T::WAVES];
+    const v2i *slots = t.slots;
+    if constexpr (MODE == 1) {
+        // stage the whole table
+        copy_to_lds<BLOCK>(reinterpret_cast<const uint32_t *>(t.slots), reinterpret_cast<uint32_t *>(lds_raw),
+                           2 * ((int)t.mask + 1));
+        __syncthreads();
+        slots = reinterpret_cast<const v2i *>(lds_raw);
+    }
+    const uint32_t *lds_words = reinterpret_cast<const uint32_t *>(lds_raw);
+    const int bitmap_words = (int)direct_bitmap_words(t.span);
+    if constexpr (MODE == 3 || MODE == 4) {
+        // stage the bitmap, and the payloads, which follow it in memory
+        copy_to_lds<BLOCK>(t.bitmap, reinterpret_cast<uint32_t *>(lds_raw),
+                           bitmap_words + (MODE == 4 ? (int)t.span : 0));
+        __syncthreads();
+    }
+    uint64_t sum = 0, cnt = 0;
+    probe_tiles<BLOCK, IPT, MODE, PP>(t, slots, lds_words, fk, pp, n, n_tiles, sum, cnt);
     const uint64_t bs = block_sum_u64<BLOCK>(sum, red);
     __syncthreads();
     const uint64_t bc = block_sum_u64<BLOCK>(cnt, red);
@@ -547,6 +559,75 @@ static hipError_t probe_t(const LaunchCfg &cfg_in, const crystal_ht &ht, const i
 // 782 us, 16 MB 1,767 -> 962 us, 32 MB 2,110 -> 1,330 us.  What bounds it is
 // the line each probe moves from L2 to the CU (a table within L2 takes 600 us)
 // and the compaction of the keys, about 45 us per slice.
+//
+// That holds for keys spread over the table.  When they are not, the gathers
+// find their lines in L2 or share them, and a slice's workgroups may get most
+// of the keys: keys_are_spread looks at a sample, and if it says no, every
+// workgroup probes the keys of its own tiles as ht_probe_kernel does.  2^27
+// keys, in us, always sliced / now (unsliced): 16 MB direct sorted 2,161/178
+// (179), 90% one key 2,183/304 (302), 8,192-key windows 942/472 (460), Zipf
+// 1,105/1,127 (1,152); 32 MB linear sorted 728/286 (289), 90% one key 1,907/326
+// (322), half one key 1,419/1,111 (1,108).  Spread keys lose nothing by it.
+
+// Whether the probe keys fk[0..n) are spread over the table, from a sample of
+// 32 groups of 64 neighbouring keys: at least three quarters of the sample have
+// a line of the table of their own.  Groups in ascending order and (direct
+// tables) groups within 4 MB of payloads count as not spread, since neighbours
+// in the column then share an XCD's L2.  (Three quarters: with half of the keys
+// equal four slices still gain 17%, eight lose 28%; with a fifth of them sorted
+// or equal both gain.)  All workgroups read the same sample and come to the same
+// answer.  seen: 2^kSeenLg bits of LDS; total: one word.
+// Called by the whole workgroup, ends with a barrier.
+constexpr uint32_t kSeenLg = 15;
+
+template <int BLOCK, int KIND>
+__device__ __forceinline__ bool keys_are_spread(const DevTable &t, const int32_t *__restrict__ fk, int64_t n,
+                                                uint32_t *seen, uint32_t *total) {
+    constexpr int W = BLOCK / kWave, kGroups = 32;
+    const int w = (int)threadIdx.x / kWave;
+    const uint32_t lane = lane_id();
+    const int64_t all = n / kWave;  // whole groups
+    const int groups = all < kGroups ? (int)all : kGroups;
+    int32_t key[kGroups / W];
+#pragma unroll
+    for (int i = 0; i < kGroups / W; ++i) {
+        const int g = w + i * W;
+        key[i] = g < groups ? fk[all * g / groups * kWave + lane] : 0;
+    }
+    for (uint32_t i = threadIdx.x; i < (1u << kSeenLg) / 32; i += BLOCK) seen[i] = 0u;
+    if (threadIdx.x == 0) *total = 0u;
+    __syncthreads();
+    uint32_t mine = 0;
+#pragma unroll
+    for (int i = 0; i < kGroups / W; ++i) {
+        if (w + i * W >= groups) break;
+        const int32_t k = key[i], before = __shfl_up(k, 1);
+        uint32_t line;
+        bool counts = ballot(lane > 0 && k < before) != 0, in = true;
+        if constexpr (KIND == CRYSTAL_HT_LINEAR) {
+            line = hash_slot(k, t.shift) >> 4;  // 16 slots
+            in = k != kEmptyKey;
+        } else {
+            const uint32_t off = (uint32_t)k - (uint32_t)t.key_min;
+            in = (int64_t)off < t.span;
+            line = off >> 5;  // 32 payloads
+            constexpr uint32_t kReach = 1u << 19;  // payloads
+            const uint32_t first = __builtin_amdgcn_readfirstlane(off);
+            counts = counts && ballot(in && off - first + kReach > 2 * kReach) != 0;
+        }
+        if (counts && in) {
+            const uint32_t h = line * 2654435761u >> (32 - kSeenLg), bit = 1u << (h & 31u);
+            mine += (atomicOr(seen + (h >> 5), bit) & bit) ? 0u : 1u;
+        }
+    }
+    const uint32_t sum = (uint32_t)wave_sum_u64(mine);
+    if (lane == 0) atomicAdd(total, sum);
+    __syncthreads();
+    const bool spread = 4u * *total >= 3u * (uint32_t)(groups * kWave);
+    __syncthreads();
+    return spread;
+}
+
 template <int BLOCK, int IPT, int KIND, bool PP, int LG>
 __global__ __launch_bounds__(BLOCK) void ht_probe_sliced_kernel(DevTable t, const int32_t *__restrict__ fk,
                                                                 const int32_t *__restrict__ pp, int64_t n,
@@ -558,6 +639,11 @@ __global__ __launch_bounds__(BLOCK) void ht_probe_sliced_kernel(DevTable t, cons
     constexpr uint32_t kQ = 2 * D * kWave;     // slice queue: fewer than D * 64 left over, then at most D * 64 more
     constexpr uint32_t kR = 2 * kWave;         // retry queue: fewer than 64 left over, then at most 64 more
     constexpr uint32_t kPieceLg = 11;          // direct: 2^11 payloads, 8 KB
+    // up to so many keys the table is probed in slices whatever the keys: the
+    // sample takes 1.5 us, and a short probe is no slower for them (in us, sliced /
+    // unsliced: 2^18 keys 8-13 / 10-40, four slices 2^20 keys 10-16 / 11-40; eight
+    // slices, 2^20 times mostly one key 24 / 12)
+    constexpr int64_t kSampleFrom = int64_t(1) << (LG == 3 ? 18 : 20);
     __shared__ int32_t q_key[T::WAVES][kQ];
     __shared__ int32_t q_pv[PP ? T::WAVES : 1][PP ? kQ : 1];
     __shared__ int32_t r_key[kLinear ? T::WAVES : 1][kR];
@@ -569,6 +655,7 @@ __global__ __launch_bounds__(BLOCK) void ht_probe_sliced_kernel(DevTable t, cons
     int32_t *my_rkey = r_key[kLinear ? w : 0], *my_rpv = r_pv[kLinear && PP ? w : 0];
     uint32_t *my_rslot = r_slot[kLinear ? w : 0];
     const uint32_t lane = lane_id();
+    __shared__ uint32_t total;
     const uint32_t slice = blockIdx.x & ((1u << LG) - 1u);
     uint32_t head = 0, tail = 0, rhead = 0, rtail = 0;  // queue cursors, equal in every lane of the wave
     uint64_t sum = 0, cnt = 0;
@@ -603,19 +690,8 @@ __global__ __launch_bounds__(BLOCK) void ht_probe_sliced_kernel(DevTable t, cons
         }
         rhead += count;
     };
-    // probe the oldest `count` (at most D * 64) keys of the slice queue
-    auto drain = [&](uint32_t count) {
-        int32_t key[D], pv[PP ? D : 1];
-        uint32_t ok = 0;
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            const uint32_t j = (uint32_t)d * kWave + lane;
-            const uint32_t i = (head + j) & (kQ - 1u);
-            key[d] = my_key[i];
-            if constexpr (PP) pv[d] = my_pv[i];
-            ok |= (uint32_t)(j < count) << d;
-        }
-        head += count;
+    // probe the keys of `ok`, D per lane
+    auto probe = [&](const int32_t(&key)[D], const int32_t(&pv)[PP ? D : 1], uint32_t ok) {
         if constexpr (kLinear) {
             typedef int32_t v4i_8 __attribute__((ext_vector_type(4), aligned(8)));
             uint32_t slot[D];
@@ -676,6 +752,21 @@ __global__ __launch_bounds__(BLOCK) void ht_probe_sliced_kernel(DevTable t, cons
             cnt += (uint64_t)__popc(ok);
         }
     };
+    // probe the oldest `count` (at most D * 64) keys of the slice queue
+    auto drain = [&](uint32_t count) {
+        int32_t key[D], pv[PP ? D : 1];
+        uint32_t ok = 0;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const uint32_t j = (uint32_t)d * kWave + lane;
+            const uint32_t i = (head + j) & (kQ - 1u);
+            key[d] = my_key[i];
+            if constexpr (PP) pv[d] = my_pv[i];
+            ok |= (uint32_t)(j < count) << d;
+        }
+        head += count;
+        probe(key, pv, ok);
+    };
     auto run_tile = [&](int64_t tile, const ProbeRegs<IPT, PP> &r) {
         const bool full = (tile + 1) * T::ITEMS <= n;
         const uint32_t valid = valid_mask<BLOCK, IPT>(tile * T::ITEMS, n);
@@ -705,7 +796,9 @@ __global__ __launch_bounds__(BLOCK) void ht_probe_sliced_kernel(DevTable t, cons
         if constexpr (PP) block_load<BLOCK, IPT, false>(pp, tile * T::ITEMS, n, r.pv);
     };
     const int64_t stride = gridDim.x >> LG;
-    int64_t tile = blockIdx.x >> LG;
+    static_assert(T::WAVES * kQ * 32 >= 1u << kSeenLg, "the sample's bits lie in the slice queues");
+    const bool sliced = n <= kSampleFrom || keys_are_spread<BLOCK, KIND>(t, fk, n, (uint32_t *)q_key, &total);
+    int64_t tile = sliced ? blockIdx.x >> LG : n_tiles;
     ProbeRegs<IPT, PP> ra, rb;
     if (tile < n_tiles) load(tile, ra);
     while (tile < n_tiles) {
@@ -719,6 +812,9 @@ __global__ __launch_bounds__(BLOCK) void ht_probe_sliced_kernel(DevTable t, cons
     }
     if (tail != head) drain(tail - head);
     if (rtail != rhead) retry(rtail - rhead);
+    if (!sliced)
+        probe_tiles<BLOCK, 16, kLinear ? 0 : 2, PP>(t, t.slots, nullptr, fk, pp, n, (n + 16 * BLOCK - 1) / (16 * BLOCK), sum,
+                                                    cnt);
     sum = wave_sum_u64(sum);
     cnt = wave_sum_u64(cnt);
     if (lane == 0) {

@@ -377,3 +377,59 @@ def test_select_stable_shares_exact_scratch(block, ipt):
     out, cnt = cx.select(dev(y), 0, 2 ** 30, stable=True, scratch=guarded[:need])
     check_select(out, cnt, y, 0, 2 ** 30, True)
     assert bool((guarded[need:] == 0xFF).all())
+
+
+# ------------------------------------- probes of large tables, keys not spread --
+def _columns(dim, n, seed):
+    """Probe columns whose keys are spread over the table or are not."""
+    rng = np.random.default_rng(seed)
+    u = rng.integers(0, dim, size=n)
+    i = np.arange(n, dtype=np.int64)
+    hot = np.where(rng.random(n) < 0.9, dim // 3, u)
+    return {"spread": u, "sorted": i * dim // n, "in turn": i % dim, "one key": np.full(n, dim - 1), "hot": hot,
+            "windows": i * (dim - 4096) // n + u % 4096,
+            "half sorted": np.where(i < n // 2, i * dim // n, u), "missing": u + dim}
+
+
+@pytest.mark.parametrize("kind,dim", [(cx.HT_LINEAR, 1 << 19), (cx.HT_LINEAR, (1 << 20) + 1),
+                                      (cx.HT_DIRECT, (1 << 20) + 1), (cx.HT_DIRECT, (1 << 21) + 7)])
+@pytest.mark.parametrize("n", [(1 << 18) + 65, (1 << 20) + 3 * 16_384 + 1])
+def test_probe_of_large_tables_with_keys_not_spread(kind, dim, n):
+    """The sample decides whether the table is probed in slices; both ways are
+    exact, with and without a probe payload, on whole and partial tiles."""
+    announce("probe columns", kind, dim, n)
+    rng = np.random.default_rng(dim)
+    key = rng.permutation(dim).astype(np.int32)
+    val = rng.integers(I32_MIN, I32_MAX, size=dim, dtype=np.int32, endpoint=True)
+    ht = cx.HashTable(kind, dim, 0, dim - 1)
+    cx.check_status(ht.build(dev(key), dev(val)))
+    pv = rng.integers(I32_MIN, I32_MAX, size=n, dtype=np.int32, endpoint=True)
+    for name, fk in _columns(dim, n, n).items():
+        fk = fk.astype(np.int32)
+        assert tuple(ht.probe(dev(fk)).cpu().tolist()) == oracle.join_sum(key, val, fk), name
+        assert tuple(ht.probe(dev(fk), dev(pv)).cpu().tolist()) == oracle.join_sum(key, val, fk, pval=pv), name
+
+
+@pytest.mark.parametrize("kind,dim", [(cx.HT_LINEAR, 1 << 21), (cx.HT_DIRECT, 1 << 21), (cx.HT_DIRECT, 1 << 22)])
+def test_probe_of_keys_not_spread_is_no_slower_than_of_spread_keys(kind, dim):
+    """Sorted, clustered and hot keys share lines of the table, so their probes
+    take no longer than those of keys spread over it (a tenth for noise)."""
+    from paper_2003_01178_amd import autotune
+    announce("probe times", kind, dim)
+    n = 1 << 25
+    key = torch.arange(dim, dtype=torch.int32, device="cuda")
+    ht = cx.HashTable(kind, dim, 0, dim - 1)
+    cx.check_status(ht.build(key, key))
+    i = torch.arange(n, device="cuda")
+    u = torch.randint(0, dim, (n,), device="cuda")
+    out = torch.zeros(2, dtype=torch.int64, device="cuda")
+
+    def us(fk):
+        fk = fk.to(torch.int32)
+        return min(autotune.time_graph_ms(lambda s: ht.probe(fk, out=out, stream=s), reps=5, per_graph=2)
+                   for _ in range(3)) * 1e3
+
+    most = 1.1 * us(u)
+    for name, fk in (("sorted", i * dim // n), ("hot", torch.where(u % 10 < 9, dim // 3, u)),
+                     ("one piece", u % 2048 + 4096)):
+        assert us(fk) <= most, name
