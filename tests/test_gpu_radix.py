@@ -438,3 +438,21 @@ def test_histogram_time_grows_with_the_input():
     most = 1.25 * histogram_us(10_000_000)
     for n in (1 << 20, 1 << 22, 1 << 23):
         assert histogram_us(n) <= most, n
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3])
+def test_unstable_partition_by_few_digits_is_no_slower_than_stable(bits):
+    """Few digits: an order that may be any takes no longer than the stable one
+    (a tenth for noise)."""
+    announce("radix unstable times", bits)
+    n = 1 << 25
+    lib = cx.load()
+    k = torch.randint(-(1 << 31), 1 << 31, (n,), device="cuda", dtype=torch.int32)
+    ok, ov = torch.empty_like(k), torch.empty_like(k)
+    scratch = torch.empty(lib.crystal_radix_partition_scratch_bytes(n), dtype=torch.uint8, device="cuda")
+
+    def us(fn):
+        return graph_us(lambda s: cx._check(fn(cx._ptr(k), cx._ptr(k), n, 8, bits, cx._ptr(ok), cx._ptr(ov), None,
+                                               cx._ptr(scratch), scratch.numel(), cx._stream(s)), "partition"))
+
+    assert us(lib.crystal_radix_partition_unstable) <= 1.1 * us(lib.crystal_radix_partition)
