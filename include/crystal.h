@@ -638,7 +638,7 @@ crystal_status crystal_sort_pairs_msb(const uint32_t *keys, const uint32_t *vals
 /* workgroups per compute unit that stride over the tiles.                  */
 /* ------------------------------------------------------------------------ */
 enum {
-    CRYSTAL_K_SELECT = 0,
+    CRYSTAL_K_SELECT = 0,             /* both selections; untuned, each has its own shape */
     CRYSTAL_K_PROJECT = 1,
     CRYSTAL_K_HT_PROBE = 2,
     CRYSTAL_K_GROUPBY = 3,

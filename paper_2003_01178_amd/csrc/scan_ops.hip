@@ -448,11 +448,7 @@ int64_t select_tile_items(const LaunchCfg &cfg) { return (int64_t)cfg.block * cf
 hipError_t launch_select(const LaunchCfg &cfg, const int32_t *in, int64_t n, int32_t lo, int32_t hi,
                          int32_t *out, int64_t *count, uint64_t *status_words, bool stable, hipStream_t s) {
     if (n == 0 || lo > hi) return fill_u64((uint64_t *)count, 1, 0ull, s);
-    // The stable kernel waits once per tile: the shape tuned for the unordered
-    // one runs with twice the threads (64M rows, half of them qualifying: 512 x
-    // 16 105 us, 1024 x 16 83, 1024 x 32 91; fewer words than 512 x 16 needs).
-    const int block = stable && cfg.block == 512 && cfg.ipt == 16 ? 1024 : cfg.block;
-    switch (CRYSTAL_VARIANT_KEY(block, cfg.ipt)) {
+    switch (CRYSTAL_VARIANT_KEY(cfg.block, cfg.ipt)) {
 #define X(B, I) \
     case CRYSTAL_VARIANT_KEY(B, I): return select_t<B, I>(cfg, in, n, lo, hi, out, count, status_words, stable, s);
         CRYSTAL_VARIANTS_ALL(X)

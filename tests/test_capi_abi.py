@@ -355,3 +355,25 @@ def test_bitpacked_format_host_checks(cx):
     for width, bits in ((0, 17), (2, 4), (0, -1)):
         q.formats[0] = cx.ColFormatC(width, 0, bits, 0)
         assert lib.crystal_run_star_query(ctypes.byref(q), ctypes.c_void_p(1 << 21), st, None, 0, None) == cx.EINVAL
+
+
+def test_stable_selection_runs_the_shape_its_scratch_is_sized_for(cx):
+    """Untuned, the stable selection has shapes of its own (8,192- and, from
+    2^20 rows on, 16,384-item tiles, also with the shipped table); a tuned
+    selection shape is taken as it is, 512 x 16 too.  One 8-byte word a tile."""
+    lib = cx.load()
+    words = lambda n, items: -(-n // items) * 8 + 16  # noqa: E731
+    try:
+        for shipped in (False, True):
+            cx.tune_reset()
+            if shipped:
+                cx.tune_load(os.path.join(ROOT, "paper_2003_01178_amd", "tune", "gfx950.txt"))
+            assert cx.tune_get(cx.K_SELECT, 1 << 29) == (512, 16, 0)             # the unordered one's
+            assert lib.crystal_select_stable_scratch_bytes(64_000_003) == words(64_000_003, 16_384)
+            assert lib.crystal_select_stable_scratch_bytes(1 << 20) == words(1 << 20, 16_384)
+            assert lib.crystal_select_stable_scratch_bytes((1 << 20) - 1) == words((1 << 20) - 1, 8192)
+        for block, ipt in ((512, 16), (64, 1), (1024, 16)):
+            cx.tune_set(cx.K_SELECT, block, ipt, 0)
+            assert lib.crystal_select_stable_scratch_bytes(64_000_003) == words(64_000_003, block * ipt)
+    finally:
+        cx.tune_reset()

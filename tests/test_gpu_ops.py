@@ -433,3 +433,18 @@ def test_probe_of_keys_not_spread_is_no_slower_than_of_spread_keys(kind, dim):
     for name, fk in (("sorted", i * dim // n), ("hot", torch.where(u % 10 < 9, dim // 3, u)),
                      ("one piece", u % 2048 + 4096)):
         assert us(fk) <= most, name
+
+
+# ------------------------------------------------- stable selection, few tiles --
+@pytest.mark.parametrize("n", [1, 63, 257, 8191, 8192, 8193, 16_384, 16_385, (1 << 20) - 1, 1 << 20, (1 << 20) + 8191])
+def test_select_stable_of_few_tiles(n):
+    """One tile (which writes the count itself and uses no words), a partial
+    one after whole ones, and the sizes where the untuned shape changes; the
+    count and the scratch hold something else before."""
+    announce("select stable few tiles", n)
+    y = datagen.select_column(n, workload=3200)
+    scratch = torch.full((cx.load().crystal_select_stable_scratch_bytes(n),), 0xA5, dtype=torch.uint8, device="cuda")
+    for lo, hi in ((0, 2 ** 30), (I32_MIN, 2 ** 31 - 1), (5, 4), (-7, -1)):
+        count = torch.full((1,), 77, dtype=torch.int64, device="cuda")
+        out, cnt = cx.select(dev(y), lo, hi, stable=True, count=count, scratch=scratch)
+        check_select(out, cnt, y, lo, hi, True)
