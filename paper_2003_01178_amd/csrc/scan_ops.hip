@@ -257,10 +257,19 @@ __global__ __launch_bounds__(BLOCK) void select_kernel(const int32_t *__restrict
 #pragma unroll
         for (int c = 0; c < C; ++c) load_vec<V, true>(in + i0 + c * (kWave * V), &v[c * V]);
     } else {
+        // vectors as far as the column goes, then its last items
 #pragma unroll
-        for (int k = 0; k < IPT; ++k) {
-            const int64_t i = i0 + (k / V) * (kWave * V) + k % V;
-            v[k] = in[i < n ? i : n - 1];
+        for (int c = 0; c < C; ++c) {
+            const int64_t i = i0 + c * (kWave * V);
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[c * V + e] = 0;
+            if (i + V <= n) {
+                load_vec<V, true>(in + i, &v[c * V]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < V; ++e)
+                    if (i + e < n) v[c * V + e] = in[i + e];
+            }
         }
     }
     uint64_t m[IPT];
@@ -287,7 +296,7 @@ __global__ __launch_bounds__(BLOCK) void select_kernel(const int32_t *__restrict
         before = i == w ? total : before;
         total += t;
     }
-    if (threadIdx.x == 0) word_store(sums.tile + tile, kPublished | total);
+    if (threadIdx.x == 0 && n_tiles > 1) word_store(sums.tile + tile, kPublished | total);
     // BlockShuffle: matches to their tile positions in LDS
 #pragma unroll
     for (int c = 0; c < C; ++c) {
@@ -303,14 +312,17 @@ __global__ __launch_bounds__(BLOCK) void select_kernel(const int32_t *__restrict
     // the matches are placed, while fewer words are there, costs more than the
     // wait it saves: 110 us)
     if (w == W - 1) {
-        const uint64_t ob = matches_before(sums, tile, n_tiles, total);
+        const uint64_t ob = n_tiles > 1 ? matches_before(sums, tile, n_tiles, total) : 0ull;
         if (lane == 0) out_base = ob;
     }
     __syncthreads();
     const uint64_t ob = out_base;
     if (ob != ~0ull) store_run<BLOCK>(buf, total, out + ob);
-    // the count was zero: the last tile's total, or -1 from any tile that gave up
-    if (threadIdx.x == 0 && (ob == ~0ull || tile == n_tiles - 1))
+    // a single tile's count is stored; otherwise it was zero and becomes the last
+    // tile's total, or -1 from any tile that gave up
+    if (n_tiles == 1) {
+        if (threadIdx.x == 0) *count_out = total;
+    } else if (threadIdx.x == 0 && (ob == ~0ull || tile == n_tiles - 1))
         atomicOr((unsigned long long *)count_out, ob == ~0ull ? ~0ull : ob + total);
 }
 
@@ -417,9 +429,11 @@ static hipError_t select_t(const LaunchCfg &cfg, const int32_t *in, int64_t n, i
     hipError_t e;
     if (stable) {
         const TileSums sums(st, n_tiles);
-        const int64_t words = ((const char *)(sums.tile + n_tiles) - (const char *)st + 7) / 8;  // at most n_tiles
-        e = zero_and_word(st, words, (uint64_t *)count, s);
-        if (e != hipSuccess) return e;
+        if (n_tiles > 1) {  // a single tile needs no words: one launch (1,000 rows 7.7 -> 4.2 us)
+            const int64_t words = ((const char *)(sums.tile + n_tiles) - (const char *)st + 7) / 8;  // at most n_tiles
+            e = zero_and_word(st, words, (uint64_t *)count, s);
+            if (e != hipSuccess) return e;
+        }
         hipLaunchKernelGGL((select_kernel<BLOCK, IPT>), dim3((unsigned)n_tiles), dim3(BLOCK), 0, s, in, n,
                            lo, hi, out, sums, count, n_tiles);
     } else {

@@ -448,3 +448,19 @@ def test_select_stable_of_few_tiles(n):
         count = torch.full((1,), 77, dtype=torch.int64, device="cuda")
         out, cnt = cx.select(dev(y), lo, hi, stable=True, count=count, scratch=scratch)
         check_select(out, cnt, y, lo, hi, True)
+
+
+@pytest.mark.parametrize("n", [1, 1000, 8192])
+def test_select_stable_of_one_tile_is_no_slower_than_unordered(n):
+    """A single tile has no predecessors to wait for."""
+    from paper_2003_01178_amd import autotune
+    announce("select stable times", n)
+    x = dev(datagen.select_column(n))
+    out, count = torch.empty_like(x), torch.zeros(1, dtype=torch.int64, device="cuda")
+    scratch = torch.empty(1 << 12, dtype=torch.uint8, device="cuda")
+
+    def us(stable):
+        return min(autotune.time_graph_ms(lambda s: cx.select(x, 0, 2 ** 30, out=out, count=count, stable=stable,
+                                                              scratch=scratch, stream=s)) for _ in range(3)) * 1e3
+
+    assert us(True) <= 1.05 * us(False)
