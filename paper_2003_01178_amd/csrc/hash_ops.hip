@@ -530,7 +530,10 @@ static hipError_t probe_t(const LaunchCfg &cfg_in, const crystal_ht &ht, const i
         all = ht.has_payload && with_payload <= lds_max;
         if (all) table_bytes = with_payload;
     }
-    const bool stage = table_bytes <= lds_max;
+    // a direct table's copy costs a short probe more than its gathers (38,000 and
+    // 2^20 keys, in us, staged / not: 1,000 probes 9.3/8.5 and 9.1/8.4, 4,096
+    // 9.6/9.3 and 9.9/9.9, 6,000 10.0/10.4 and 10.7/11.4)
+    const bool stage = table_bytes <= lds_max && (ht.kind == CRYSTAL_HT_LINEAR || n >= 5000);
     if (stage && cfg.grid_per_cu <= 0) cfg.grid_per_cu = 1;  // stage once per resident workgroup
     const int64_t grid = grid_for(n_tiles, cfg);
     if (grid == 0) return hipSuccess;

@@ -464,3 +464,39 @@ def test_select_stable_of_one_tile_is_no_slower_than_unordered(n):
                                                               scratch=scratch, stream=s)) for _ in range(3)) * 1e3
 
     assert us(True) <= 1.05 * us(False)
+
+
+@pytest.mark.parametrize("dim,other,has_payload", [(38_000, 200_000, True), (1 << 20, 1_500_000, False)])
+def test_short_probe_of_a_direct_table_does_not_wait_for_its_copy(dim, other, has_payload):
+    """1,000 probes take no longer into a table whose copy would fill LDS than
+    into one of the same kind of which less or nothing fits (a twentieth for
+    noise)."""
+    from paper_2003_01178_amd import autotune
+    announce("probe short times", dim)
+    out = torch.zeros(2, dtype=torch.int64, device="cuda")
+    fk = torch.randint(0, dim, (1000,), device="cuda", dtype=torch.int32)
+
+    def us(keys):
+        key = torch.arange(keys, dtype=torch.int32, device="cuda")
+        ht = cx.HashTable(cx.HT_DIRECT, keys, 0, keys - 1, has_payload=has_payload)
+        cx.check_status(ht.build(key, key if has_payload else None))
+        return min(autotune.time_graph_ms(lambda s: ht.probe(fk, out=out, stream=s)) for _ in range(5)) * 1e3
+
+    assert us(dim) <= 1.05 * us(other)
+
+
+@pytest.mark.parametrize("n", [4999, 5000])
+@pytest.mark.parametrize("dim,has_payload", [(2049, True), (38_000, True), (40_001, True), (1 << 20, False)])
+def test_probe_of_a_direct_table_staged_or_not(dim, has_payload, n):
+    """Both sides of the number of probes from which a table is staged."""
+    announce("probe stage", dim, has_payload, n)
+    rng = np.random.default_rng(dim + n)
+    key = rng.permutation(dim).astype(np.int32)[: dim - dim // 3]
+    val = rng.integers(I32_MIN, I32_MAX, size=key.size, dtype=np.int32, endpoint=True)
+    fk = rng.integers(-dim // 4, dim + dim // 4, size=n).astype(np.int32)
+    pv = rng.integers(I32_MIN, I32_MAX, size=n, dtype=np.int32, endpoint=True)
+    ht = cx.HashTable(cx.HT_DIRECT, dim, 0, dim - 1, has_payload=has_payload)
+    cx.check_status(ht.build(dev(key), dev(val) if has_payload else None))
+    want = val if has_payload else np.zeros_like(val)
+    assert tuple(ht.probe(dev(fk)).cpu().tolist()) == oracle.join_sum(key, want, fk)
+    assert tuple(ht.probe(dev(fk), dev(pv)).cpu().tolist()) == oracle.join_sum(key, want, fk, pval=pv)
