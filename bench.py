@@ -823,14 +823,16 @@ def main():
         # HBM bytes are the key stream alone.  A larger table costs one
         # 128-byte line per probe (section 4.3's model).
         llc_resident = ht.nbytes <= LLC_BYTES
+        slices = ht.probe_slices()  # such tables have a kernel, and a tile, of their own
         b = 4 * n + (0 if llc_resident else n * FETCH_BYTES)
         if llc_resident:
             roof["note"] = "table resident in the last-level cache: probes are bound by its random-access rate"
         result.update(metric="probes/s (hash join probe + sum)", value=n * K / elapsed, unit="probes/s",
                       ms_per_step=elapsed / K * 1e3, dtype="int32",
                       config={"workload": f"join probe: D={d} ({args.kind}, table {ht.nbytes} B), 2^28 probes",
-                              "probes": n, "table_bytes": ht.nbytes, "tile": list(cx.tune_get(cx.K_HT_PROBE, n))})
-        roof.update(kernel="crystal::ht_probe_kernel", achieved=b / (kern_ms * 1e-3) / 1e9, algorithmic_bytes=b,
+                              "probes": n, "table_bytes": ht.nbytes, "slices": slices,
+                              "tile": [1024, 16, 1] if slices else list(cx.tune_get(cx.K_HT_PROBE, n))})
+        roof.update(kernel="crystal::ht_probe_sliced_kernel" if slices else "crystal::ht_probe_kernel", achieved=b / (kern_ms * 1e-3) / 1e9, algorithmic_bytes=b,
                     kernel_ms=kern_ms)
 
     elif args.workload == "copy":

@@ -214,6 +214,13 @@ crystal_status crystal_ht_probe(const crystal_ht *ht, const int32_t *fk,
                                 const int32_t *probe_payload, int64_t n,
                                 int64_t *out_sum, int64_t *out_matches, void *stream);
 
+/* How crystal_ht_probe looks `ht` up, with or without a probe payload: 0, by
+ * the kernel whose tile shape CRYSTAL_K_HT_PROBE tunes, or the number of slices
+ * of a table larger than an XCD's L2 cache (8 to 64 MB of slots, 4 to 32 MB of
+ * payloads), which a kernel of a fixed shape probes one after another where a
+ * sample of the keys is spread over the table. */
+int32_t crystal_ht_probe_slices(const crystal_ht *ht, int32_t with_payload);
+
 /* ------------------------------------------------------------------------ */
 /* Dense group-by aggregate (the aggregation table of section 5.3 in the     */
 /* dense form small group keys allow):  sums[group[i]] += value[i]  (int64). */
@@ -640,7 +647,7 @@ crystal_status crystal_sort_pairs_msb(const uint32_t *keys, const uint32_t *vals
 enum {
     CRYSTAL_K_SELECT = 0,             /* both selections; untuned, each has its own shape */
     CRYSTAL_K_PROJECT = 1,
-    CRYSTAL_K_HT_PROBE = 2,
+    CRYSTAL_K_HT_PROBE = 2,           /* probes that crystal_ht_probe_slices says 0 for */
     CRYSTAL_K_GROUPBY = 3,
     CRYSTAL_K_STAR = 4,
     CRYSTAL_K_SHARED_SCAN = 5,        /* shared-scan batches of grouped templates */

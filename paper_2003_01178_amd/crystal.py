@@ -133,6 +133,7 @@ def _declare(lib):
         "crystal_ht_build_batch": (c_i32, [P(BuildItemC), c_i32, c_vp, c_vp]),
         "crystal_ht_build_batch_fused": (c_i32, [P(BuildItemC), c_i32, P(P(HT)), c_i32, c_vp, c_i64, c_vp, c_vp]),
         "crystal_ht_probe": (c_i32, [P(HT), c_vp, c_vp, c_i64, c_vp, c_vp, c_vp]),
+        "crystal_ht_probe_slices": (c_i32, [P(HT), c_i32]),
         "crystal_groupby_agg": (c_i32, [c_vp, c_vp, c_i64, c_i64, c_vp, c_vp, c_vp]),
         "crystal_star_query_scratch_bytes": (ctypes.c_size_t, [P(StarQueryC)]),
         "crystal_run_star_query": (c_i32, [P(StarQueryC), c_vp, c_vp, c_vp, ctypes.c_size_t, c_vp]),
@@ -317,6 +318,10 @@ class HashTable:
                                     Range(int(filter[0]), int(filter[1])), keys.numel(),
                                     _ptr(status), _stream(stream)), "crystal_ht_build")
         return status
+
+    def probe_slices(self, with_payload=False):
+        """Slices in which a probe takes this table, 0: by the tuned kernel."""
+        return load().crystal_ht_probe_slices(ctypes.byref(self.desc), 1 if with_payload else 0)
 
     def probe(self, fk, probe_payload=None, out=None, stream=None):
         """Q4 probe: device int64[2] = (sum, matches)."""

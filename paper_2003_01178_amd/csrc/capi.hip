@@ -469,6 +469,10 @@ crystal_status crystal_ht_probe(const crystal_ht *ht, const int32_t *fk, const i
                                     (uint64_t *)out_sum, (uint64_t *)out_matches, as_stream(stream)));
 }
 
+int32_t crystal_ht_probe_slices(const crystal_ht *ht, int32_t with_payload) {
+    return ht ? ht_probe_slices(*ht, with_payload != 0) : 0;
+}
+
 crystal_status crystal_groupby_agg(const int32_t *group, const int32_t *value, int64_t n,
                                    int64_t n_groups, int64_t *sums, int32_t *status, void *stream) {
     if (n < 0 || n_groups < 1 || !sums || !status ||

@@ -877,6 +877,11 @@ static int probe_slices_lg(const crystal_ht &ht, bool pp) {
     return pp || bytes <= (linear ? 16 : 8) * mb ? 2 : 3;
 }
 
+int ht_probe_slices(const crystal_ht &ht, bool with_payload) {
+    const int lg = probe_slices_lg(ht, with_payload);
+    return lg ? 1 << lg : 0;
+}
+
 hipError_t launch_ht_probe(const LaunchCfg &cfg, const crystal_ht &ht, const int32_t *fk,
                            const int32_t *probe_payload, int64_t n, uint64_t *sum, uint64_t *count,
                            hipStream_t s) {

@@ -103,6 +103,8 @@ hipError_t launch_ht_build_batch_fused(const crystal_ht_build_item *items, int n
 hipError_t launch_ht_probe(const LaunchCfg &cfg, const crystal_ht &ht, const int32_t *fk,
                            const int32_t *probe_payload, int64_t n, uint64_t *sum, uint64_t *count,
                            hipStream_t s);
+// slices of a probed table, 0: probed by the tuned shape
+int ht_probe_slices(const crystal_ht &ht, bool with_payload);
 hipError_t launch_groupby(const LaunchCfg &cfg, const int32_t *group, const int32_t *value,
                           int64_t n, int64_t n_groups, uint64_t *sums, int32_t *status,
                           hipStream_t s);

@@ -1,0 +1,42 @@
+"""What the autotuner sweeps and writes, as far as it needs no GPU."""
+import ctypes
+
+import pytest
+
+from paper_2003_01178_amd import autotune
+from paper_2003_01178_amd import crystal as cx
+
+
+def table(kind, keys, has_payload=True):
+    """A table's description, without its memory."""
+    desc = cx.HT()
+    assert cx.load().crystal_ht_init(ctypes.byref(desc), kind, keys, 0, keys - 1, int(has_payload)) == cx.OK
+    return desc
+
+
+def slices(desc, with_payload=False):
+    return cx.load().crystal_ht_probe_slices(ctypes.byref(desc), int(with_payload))
+
+
+def test_swept_probe_tables_are_probed_by_the_tuned_kernel():
+    for d in autotune.PROBE_KEYS:
+        assert slices(table(cx.HT_LINEAR, d)) == 0, d
+
+
+@pytest.mark.parametrize("kind,keys,has_payload,plain,with_payload", [
+    (cx.HT_LINEAR, 1 << 18, True, 0, 0), (cx.HT_LINEAR, (1 << 18) + 1, True, 4, 4),
+    (cx.HT_LINEAR, 1 << 20, True, 4, 4), (cx.HT_LINEAR, 1 << 21, True, 8, 4), (cx.HT_LINEAR, 1 << 22, True, 8, 0),
+    (cx.HT_LINEAR, 1 << 23, True, 0, 0), (cx.HT_DIRECT, 1 << 20, True, 0, 0), (cx.HT_DIRECT, (1 << 20) + 1, True, 4, 4),
+    (cx.HT_DIRECT, (1 << 21) + 1, True, 8, 4), (cx.HT_DIRECT, (1 << 23) + 1, True, 0, 0),
+    (cx.HT_DIRECT, 1 << 23, False, 0, 0)])
+def test_probe_slices_of_tables(kind, keys, has_payload, plain, with_payload):
+    desc = table(kind, keys, has_payload)
+    assert (slices(desc), slices(desc, True)) == (plain, with_payload)
+
+
+def test_common_winner_of_several_sweeps():
+    a = [(1.0, 256, 8, 1), (1.1, 512, 8, 1), (3.0, 1024, 16, 1)]
+    b = [(10.0, 1024, 16, 1), (11.0, 512, 8, 1), (20.0, 256, 8, 1)]
+    assert autotune.common_winner([a, b]) == (512, 8, 1)
+    assert autotune.common_winner([a, b[:1] + b[2:]]) == (256, 8, 1)     # 512 x 8 was discarded in one
+    assert autotune.common_winner([a]) == (256, 8, 1)
