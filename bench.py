@@ -928,7 +928,10 @@ def main():
             scratch = torch.empty(cx.load().crystal_sort_pairs_msb_scratch_bytes(n, 1), dtype=torch.uint8,
                                   device="cuda")
             call = lambda: cx.sort_pairs(keys, vals, out_keys=ok, out_vals=ov, scratch=scratch, msb=True)
-            passes = 2   # uniform keys: two partition levels, then the local sort (counted below)
+            # uniform keys: two partition levels, then the local sort (counted
+            # below); up to 2^27 untuned pairs, four passes from the low byte up
+            levels = n > 1 << 27 or bool(args.tune)
+            passes = 2 if levels else 4
         else:
             scratch = torch.empty(cx.load().crystal_sort_pairs_scratch_bytes(n, 1), dtype=torch.uint8,
                                   device="cuda")
@@ -948,7 +951,7 @@ def main():
         # per pass: the histogram reads the keys (4n), the shuffle reads keys and
         # values (8n) and writes them (8n); the MSB sort's local pass reads and
         # writes every pair once more (16n)
-        b = passes * 20 * n + (16 * n if args.workload == "sort" and args.msb else 0)
+        b = passes * 20 * n + (16 * n if args.workload == "sort" and args.msb and levels else 0)
         what = (f"radix partition ({'unstable' if args.unstable else 'stable'}) of 2^{n.bit_length() - 1} "
                 f"key/value pairs on {args.bits} bits at bit {args.shift}"
                 if args.workload == "partition" else

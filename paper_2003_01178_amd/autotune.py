@@ -6,7 +6,8 @@ launch stream (around replays of a graph of calls, for the calls shorter
 than their own host-side set-up); variants whose result differs from the
 first variant's are discarded.  The winner for each workload size is
 written into the library's tuning table for the size buckets nearest to
-that size, and the table is saved as a text cache (``tune/gfx950.txt``)
+that size (of the selections and the radix passes, whose built-in shapes
+depend on more than the table does, only if it gains), and the table is saved as a text cache (``tune/gfx950.txt``)
 that ``crystal.load()`` reads.
 
 Usage: ``python -m paper_2003_01178_amd.autotune [--kernels star,select,...]
@@ -123,16 +124,28 @@ def common_winner(sweeps):
     return min((sum(c), shape) for shape, c in cost.items() if len(c) == len(sweeps))[1]
 
 
+def improves(kernel, n, rows, untuned_ms, others=(), reps=10):
+    """Whether a sweep's winner is worth an entry of the table: at least 2%
+    faster than the built-in shape, and no slower (by 2%) for the other calls
+    that the entry would govern, [(call, its time untuned)]."""
+    ms, b, i, g = rows[0]
+    if ms > 0.98 * untuned_ms:
+        return False
+    cx.tune_set(kernel, b, i, g, bucket_lo=bucket(n), bucket_hi=bucket(n))
+    return all(time_ms(call, reps=reps) <= 1.02 * base for call, base in others)
+
+
 WINNERS = {}
 
 
-def assign(kernel, results):
-    """results: [(n, (b, i, g))]; cover all buckets, splitting between sizes."""
-    WINNERS[kernel] = list(results)
+def assign(kernel, results, lowest=0):
+    """results: [(n, (b, i, g))]; cover the buckets from `lowest` on, splitting
+    between sizes.  No results: no entries of this kernel."""
+    WINNERS[kernel] = list(results), lowest
     results = sorted(results)
     bks = [bucket(n) for n, _ in results]
     for k, (n, (b, i, g)) in enumerate(results):
-        lo = 0 if k == 0 else (bks[k - 1] + bks[k]) // 2 + 1
+        lo = lowest if k == 0 else (bks[k - 1] + bks[k]) // 2 + 1
         hi = 63 if k == len(results) - 1 else (bks[k] + bks[k + 1]) // 2
         cx.tune_set(kernel, b, i, g, bucket_lo=lo, bucket_hi=hi)
 
@@ -189,11 +202,17 @@ def main(argv=None):
         c = torch.empty(1, dtype=torch.int64, device="cuda")
         cands = [(128, 4), (256, 4), (256, 8), (256, 16), (512, 8), (512, 16), (1024, 8)] if args.quick else None
         # one workgroup per tile always (grid_per_cu does not apply to selection)
-        rows = sweep(cx.K_SELECT, n, lambda: cx.select(x, lo, hi, out=o, count=c), lambda: c.cpu().numpy(),
-                     candidates=cands, gpcs=(0,), reps=args.reps, log=log)
-        assign(cx.K_SELECT, [(n, rows[0][1:])])
+        # an entry replaces the built-in shapes of both selections
+        words = torch.empty(n // 8 + 16, dtype=torch.uint8, device="cuda")      # of the smallest tiles
+        unordered = lambda: cx.select(x, lo, hi, out=o, count=c)  # noqa: E731
+        stable = lambda: cx.select(x, lo, hi, out=o, count=c, stable=True, scratch=words)  # noqa: E731
+        base, base_stable = time_ms(unordered, reps=args.reps), time_ms(stable, reps=args.reps)
+        rows = sweep(cx.K_SELECT, n, unordered, lambda: c.cpu().numpy(), candidates=cands, gpcs=(0,), reps=args.reps,
+                     log=log)
+        worth = improves(cx.K_SELECT, n, rows, base, [(stable, base_stable)], args.reps)
+        assign(cx.K_SELECT, [(n, rows[0][1:])] if worth else [])
         report["select_2^29"] = rows[:8]
-        del x, o
+        del x, o, words
         torch.cuda.empty_cache()
     if "project" in kernels:
         n = 1 << 29
@@ -283,10 +302,18 @@ def main(argv=None):
         ok, ov = torch.empty_like(keys), torch.empty_like(vals)
         scratch = torch.empty(cx.load().crystal_radix_partition_scratch_bytes(n) * 4, dtype=torch.uint8,
                               device="cuda")
-        rows = sweep(cx.K_RADIX, n, lambda: cx.radix_partition(keys, 0, 8, vals=vals, out_keys=ok, out_vals=ov,
-                                                               scratch=scratch),
-                     lambda: ok[:: 1 << 12].cpu().numpy(), gpcs=(0, 1, 2), reps=args.reps, log=log)
-        assign(cx.K_RADIX, [(n, rows[0][1:])])
+        # The built-in shapes depend on the size and on whether there are values,
+        # and any entry keeps the most-significant-digit sort on its levels: an
+        # entry only for inputs as long as the swept one, where the levels run
+        # anyway, and only if it gains.
+        pairs = lambda: cx.radix_partition(keys, 0, 8, vals=vals, out_keys=ok, out_vals=ov,  # noqa: E731
+                                           scratch=scratch)
+        alone = lambda: cx.radix_partition(keys, 0, 8, out_keys=ok, scratch=scratch)  # noqa: E731
+        base, base_alone = time_ms(pairs, reps=args.reps), time_ms(alone, reps=args.reps)
+        rows = sweep(cx.K_RADIX, n, pairs, lambda: ok[:: 1 << 12].cpu().numpy(), gpcs=(0, 1, 2), reps=args.reps,
+                     log=log)
+        worth = improves(cx.K_RADIX, n, rows, base, [(alone, base_alone)], args.reps)
+        assign(cx.K_RADIX, [(n, rows[0][1:])] if worth else [], lowest=bucket(n))
         report["radix_partition_2^28"] = rows[:8]
         del keys, vals, ok, ov
         torch.cuda.empty_cache()
@@ -303,8 +330,8 @@ def main(argv=None):
     cx.tune_reset()
     for k, lo, hi, b, i, g in kept:
         cx.tune_set(k, b, i, g, bucket_lo=lo, bucket_hi=hi)
-    for kernel, results in WINNERS.items():
-        assign(kernel, results)
+    for kernel, (results, lowest) in list(WINNERS.items()):
+        assign(kernel, results, lowest)
     os.makedirs(os.path.dirname(os.path.abspath(args.out)), exist_ok=True)
     cx.tune_save(args.out)
     report["saved"] = args.out

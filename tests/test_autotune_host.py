@@ -40,3 +40,35 @@ def test_common_winner_of_several_sweeps():
     assert autotune.common_winner([a, b]) == (512, 8, 1)
     assert autotune.common_winner([a, b[:1] + b[2:]]) == (256, 8, 1)     # 512 x 8 was discarded in one
     assert autotune.common_winner([a]) == (256, 8, 1)
+
+
+@pytest.fixture
+def untuned():
+    cx.tune_reset()
+    yield
+    cx.tune_reset()
+
+
+def test_radix_entries_leave_shorter_inputs_untuned(untuned):
+    """The built-in radix shapes follow the size; an entry measured at 2^28
+    pairs governs inputs as long as that and no others."""
+    sizes = (1000, 100_003, 1 << 20, 1 << 25, (1 << 28) - 1)
+    before = [cx.tune_get(cx.K_RADIX, n) for n in sizes]
+    autotune.assign(cx.K_RADIX, [(1 << 28, (512, 16, 1))], lowest=autotune.bucket(1 << 28))
+    assert [cx.tune_get(cx.K_RADIX, n) for n in sizes] == before
+    assert cx.tune_get(cx.K_RADIX, 1 << 28) == cx.tune_get(cx.K_RADIX, 1 << 31) == (512, 16, 1)
+
+
+def test_entries_cover_all_sizes_of_a_kernel_measured_at_several(untuned):
+    autotune.assign(cx.K_STAR, [(1 << 27, (512, 8, 8)), (1 << 22, (512, 4, 8))])
+    assert cx.tune_get(cx.K_STAR, 1) == cx.tune_get(cx.K_STAR, (1 << 25) - 1) == (512, 4, 8)
+    assert cx.tune_get(cx.K_STAR, 1 << 25) == cx.tune_get(cx.K_STAR, 1 << 40) == (512, 8, 8)
+    autotune.assign(cx.K_SELECT, [])
+    assert cx.tune_get(cx.K_SELECT, 1 << 29) == (512, 16, 0)
+
+
+@pytest.mark.parametrize("winner,other,worth", [(0.97, 1.0, True), (0.99, 1.0, False), (0.5, 1.03, False)])
+def test_an_entry_has_to_gain_and_not_to_slow_other_calls(untuned, monkeypatch, winner, other, worth):
+    monkeypatch.setattr(autotune, "time_ms", lambda call, reps: call())
+    rows = [(winner, 512, 8, 0), (2.0, 256, 8, 0)]
+    assert autotune.improves(cx.K_SELECT, 1 << 29, rows, 1.0, [(lambda: other, 1.0)]) == worth
