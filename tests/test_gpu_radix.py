@@ -456,3 +456,89 @@ def test_unstable_partition_by_few_digits_is_no_slower_than_stable(bits):
                                                cx._ptr(scratch), scratch.numel(), cx._stream(s)), "partition"))
 
     assert us(lib.crystal_radix_partition_unstable) <= 1.1 * us(lib.crystal_radix_partition)
+
+
+# ------------------------------------------------------------ MSB levels --
+# With a tuned shape, and above 2^27 pairs, the most-significant-digit sort runs
+# its levels; untuned, shorter inputs take four passes from the low byte up.
+@pytest.fixture
+def levels():
+    cx.tune_set(cx.K_RADIX, 1024, 16, 0)
+
+
+def _degenerate(case, n, rng):
+    u = rng.integers(0, 1 << 32, size=n, dtype=np.uint64).astype(np.uint32)
+    if case == "all_equal":
+        return np.full(n, 0x9E3779B9, dtype=np.uint32)
+    if case == "two_values":
+        return np.where(rng.random(n) < 0.5, 7, 0xFFFFFFF0).astype(np.uint32)
+    if case == "top_byte_only":
+        return rng.integers(0, 256, size=n).astype(np.uint32) << np.uint32(24)
+    if case == "sorted":
+        return np.sort(u)
+    if case == "reversed":
+        return np.sort(u)[::-1].copy()
+    u[rng.random(n) < 0.6] = 0x12345678     # one long run beside many short segments
+    return u
+
+
+@pytest.mark.parametrize("case", ["all_equal", "two_values", "top_byte_only", "sorted", "reversed", "one_big_rest_small"])
+@pytest.mark.parametrize("n", [300_007, 3_000_017])
+def test_msb_levels_of_degenerate_digits(levels, case, n):
+    """One segment down to the last level and copied in pieces, two of them,
+    segments that are done after the first level, presorted and reversed input,
+    one segment that stays long beside many short ones."""
+    announce("msb levels degenerate", case, n)
+    rng = np.random.default_rng(n)
+    k = _degenerate(case, n, rng)
+    v = rng.integers(0, 1 << 32, size=n, dtype=np.uint64).astype(np.uint32)
+    wk, wv = oracle.sort_pairs(k, v)
+    ok, ov = cx.sort_pairs(dev(k.view(np.int32)), dev(v.view(np.int32)), msb=True)
+    assert np.array_equal(u32(ok, n), wk) and np.array_equal(u32(ov, n), wv)
+    ok, ov = cx.sort_pairs(dev(k.view(np.int32)), msb=True)
+    assert ov is None and np.array_equal(u32(ok, n), wk)
+
+
+def test_msb_levels_of_repeated_calls_share_scratch(levels):
+    """Two sorts through one scratch buffer, the second smaller: the work
+    lists, counters and chunks taken by the first must not leak into it."""
+    announce("msb levels scratch reuse")
+    scratch = torch.empty(cx.load().crystal_sort_pairs_msb_scratch_bytes(1_500_001, 1), dtype=torch.uint8,
+                          device="cuda")
+    for n in (1_500_001, 40_961, 1_000_000):
+        k, v = pairs(n, 1500 + n, key_bits=20)
+        ok, ov = cx.sort_pairs(dev(k.view(np.int32)), dev(v.view(np.int32)), scratch=scratch, msb=True)
+        wk, wv = oracle.sort_pairs(k, v)
+        assert np.array_equal(u32(ok, n), wk) and np.array_equal(u32(ov, n), wv)
+
+
+@pytest.mark.parametrize("skew", ["one long run", "few digits"])
+def test_msb_levels_of_many_chunks(levels, skew):
+    """More chunks than workgroups are resident, unevenly spread over the
+    segments, so that workgroups take a second and a third one."""
+    announce("msb levels chunks", skew)
+    n = 24_000_011
+    k = np.random.default_rng(77).integers(0, 1 << 32, size=n, dtype=np.uint64).astype(np.uint32)
+    if skew == "one long run":
+        k[n // 5:n // 5 * 4] = 0xABCD0123
+    else:
+        k &= np.uint32(0x030F00FF)          # few top digits, then none, then all
+    v = np.arange(n, dtype=np.uint32)
+    wk, wv = oracle.sort_pairs(k, v)
+    ok, ov = cx.sort_pairs(dev(k.view(np.int32)), dev(v.view(np.int32)), msb=True)
+    assert np.array_equal(u32(ok, n), wk) and np.array_equal(u32(ov, n), wv)
+    ok, _ = cx.sort_pairs(dev(k.view(np.int32)), msb=True)
+    assert np.array_equal(u32(ok, n), wk)
+
+
+@pytest.mark.parametrize("msb", [False, True])
+def test_sort_of_keys_alone_above_two_pow_27(msb):
+    """Untuned: the levels of the most-significant-digit sort, whose first pass
+    has the shape of keys alone; four passes otherwise."""
+    announce("radix keys alone", msb)
+    n = (1 << 27) + 16_385
+    torch.manual_seed(5)
+    keys = torch.randint(-(1 << 31), 1 << 31, (n,), device="cuda", dtype=torch.int32)
+    keys[n // 2:n // 2 + n // 8] = 77       # and a run of one key
+    ok, _ = cx.sort_pairs(keys, msb=msb)
+    assert np.array_equal(u32(ok, n), np.sort(u32(keys, n)))
