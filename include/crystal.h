@@ -651,7 +651,8 @@ enum {
     CRYSTAL_K_GROUPBY = 3,
     CRYSTAL_K_STAR = 4,
     CRYSTAL_K_SHARED_SCAN = 5,        /* shared-scan batches of grouped templates */
-    CRYSTAL_K_RADIX = 6,
+    CRYSTAL_K_RADIX = 6,              /* radix passes; untuned, the shape follows the size and whether
+                                       * there are values (crystal_tune_get answers for pairs) */
     CRYSTAL_K_SHARED_SCAN_SCALAR = 7, /* shared-scan batches of scalar templates  */
     CRYSTAL_K_COUNT = 8
 };

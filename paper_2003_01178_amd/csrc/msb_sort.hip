@@ -66,33 +66,6 @@ struct Ctl {
 
 __device__ __forceinline__ int task_list(uint32_t len, uint32_t bits) { return bits && len <= kSmallMax ? 0 : 1; }
 
-// Exclusive prefix over the block's threads in thread order; tmp: one word
-// per wave.  Ends with a barrier, after which tmp may be reused.
-template <int BLOCK>
-__device__ __forceinline__ uint32_t block_scan_excl(uint32_t x, uint32_t *tmp, uint32_t &total) {
-    constexpr int W = BLOCK / kWave;
-    const int lane = (int)lane_id();
-    uint32_t inc = x;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const uint32_t y = __shfl_up(inc, o);
-        if (lane >= o) inc += y;
-    }
-    const int w = (int)threadIdx.x / kWave;
-    if (lane == kWave - 1) tmp[w] = inc;
-    __syncthreads();
-    uint32_t before = 0, tot = 0;
-#pragma unroll
-    for (int i = 0; i < W; ++i) {
-        const uint32_t t = tmp[i];
-        before += i < w ? t : 0u;
-        tot += t;
-    }
-    total = tot;
-    __syncthreads();
-    return before + inc - x;
-}
-
 // ------------------------------------------------------------ work lists --
 // One workgroup: chunk counts of the level's big segments, their exclusive
 // prefix (each segment's first chunk), the level's chunk total; clears the
@@ -107,7 +80,7 @@ __global__ __launch_bounds__(1024) void msb_chunk_scan_kernel(Ctl *ctl, Seg *big
     uint32_t sum = 0;
     for (uint32_t i = s0; i < s1; ++i) sum += (big[i].len + kChunk - 1) / kChunk;
     uint32_t total;
-    uint32_t run = block_scan_excl<1024>(sum, tmp, total);
+    uint32_t run = block_exclusive_scan<1024>(sum, tmp, total);
     for (uint32_t i = s0; i < s1; ++i) {
         const uint32_t c = (big[i].len + kChunk - 1) / kChunk;
         big[i].chunk_base = run;
@@ -334,7 +307,7 @@ __global__ __launch_bounds__(kAuxBlock) void msb_scan_kernel(Ctl *ctl, const Seg
             for (uint32_t k = 0; k < kAhead; ++k) run += v[k];
         }
         uint32_t unused;
-        const uint32_t dstart = block_scan_excl<kAuxBlock>(run, tmp, unused);
+        const uint32_t dstart = block_exclusive_scan<kAuxBlock>(run, tmp, unused);
         const uint32_t at = s.start + dstart;
         uint32_t next_at = at;
         for (uint32_t j = 0; j < s.nchunks; j += kAhead) {
@@ -467,8 +440,7 @@ MsbLayout msb_layout(int64_t n, bool vals) {
     // or a big sub-segment, or at its parent's end, so there are at most
     // n / (kLocalMax - kSmallSeg) + n / kSmallSeg + (big segments of this and
     // the next level) of them.  Then the last level's copies (pieces of at
-    // most kCopy pairs of the big segments) and the single task of a short
-    // input.
+    // most kCopy pairs of the big segments).
     L.max_tasks = 3 * (2 * (n / kSmallSeg) + n / (kLocalMax - kSmallSeg) + 2 * L.max_big + 2) + n / kCopy +
                   L.max_big + 8;
     int64_t at = 0;

@@ -28,28 +28,6 @@
 namespace crystal {
 namespace {
 
-// Exclusive prefix of x over threads 0 .. BLOCK-1 in thread order; `tmp` holds
-// one word per wave.  Every thread calls it; it ends with a barrier, after
-// which tmp may be reused.
-template <int BLOCK>
-__device__ __forceinline__ uint32_t block_exclusive_scan_u32(uint32_t x, uint32_t *tmp, uint32_t &total) {
-    constexpr int W = BLOCK / kWave;
-    const uint32_t inc = wave_inclusive_scan(x);
-    const int w = threadIdx.x / kWave;
-    if (lane_id() == kWave - 1) tmp[w] = inc;
-    __syncthreads();
-    uint32_t before = 0, tot = 0;
-#pragma unroll
-    for (int i = 0; i < W; ++i) {
-        uint32_t t = tmp[i];
-        before += i < w ? t : 0u;
-        tot += t;
-    }
-    total = tot;
-    __syncthreads();
-    return before + inc - x;
-}
-
 // Tiles [t0, t1) of the chunk that column `col` of the count matrix covers.
 struct Chunk {
     int64_t t0, t1;
@@ -170,7 +148,7 @@ __global__ __launch_bounds__(kScanBlock) void radix_scan_kernel(uint32_t *__rest
             const int64_t c = c0 + k * kScanBlock + (int64_t)threadIdx.x;
             if (c0 + k * kScanBlock >= cols) break;
             uint32_t sum;
-            const uint32_t before = block_exclusive_scan_u32<kScanBlock>(v[k], tmp, sum);
+            const uint32_t before = block_exclusive_scan<kScanBlock>(v[k], tmp, sum);
             if (c < cols) row[c] = total + before;
             total += sum;
         }
@@ -201,7 +179,7 @@ __global__ __launch_bounds__(BLOCK, 8) void radix_shuffle_kernel(
         // partition starts: exclusive prefix of the digit totals (the stage is free as scratch)
         uint32_t unused;
         const uint32_t tot = (tid < kBins && (uint32_t)tid <= mask) ? totals[tid] : 0u;
-        const uint32_t dstart = block_exclusive_scan_u32<BLOCK>(tot, lds, unused);
+        const uint32_t dstart = block_exclusive_scan<BLOCK>(tot, lds, unused);
         if (tid < kBins) {
             s_run[tid] = (uint32_t)tid <= mask ? dstart + counts[(int64_t)tid * cols + block * sub] : 0u;
             if (block == 0 && part_offsets && (uint32_t)tid <= mask) part_offsets[tid] = dstart;

@@ -66,6 +66,28 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
     return x;
 }
 
+// Exclusive prefix of x over threads 0 .. BLOCK-1 in thread order; `tmp` holds
+// one word per wave.  Every thread calls it; it ends with a barrier, after
+// which tmp may be reused.
+template <int BLOCK>
+__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t *tmp, uint32_t &total) {
+    constexpr int W = BLOCK / kWave;
+    const uint32_t inc = wave_inclusive_scan(x);
+    const int w = threadIdx.x / kWave;
+    if (lane_id() == kWave - 1) tmp[w] = inc;
+    __syncthreads();
+    uint32_t before = 0, tot = 0;
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+        uint32_t t = tmp[i];
+        before += i < w ? t : 0u;
+        tot += t;
+    }
+    total = tot;
+    __syncthreads();
+    return before + inc - x;
+}
+
 // Lanes of the wave whose 8-bit digit equals the calling lane's.  Per bit: the
 // bit as 0 or -1 (one signed bit-field extract), its ballot (one compare), and
 // one three-operand bit operation per half of the mask.
