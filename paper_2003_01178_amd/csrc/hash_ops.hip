@@ -570,22 +570,20 @@ static hipError_t probe_t(const LaunchCfg &cfg_in, const crystal_ht &ht, const i
 // keys, in us, always sliced / now (unsliced): 16 MB direct sorted 2,161/178
 // (179), 90% one key 2,183/304 (302), 8,192-key windows 942/472 (460), Zipf
 // 1,105/1,127 (1,152); 32 MB linear sorted 728/286 (289), 90% one key 1,907/326
-// (322), half one key 1,419/1,111 (1,108).  Spread keys lose nothing by it.
+// (322), half one key 1,419/1,111 (1,108).  Spread keys lose 1% to the sample.
 
 // Whether the probe keys fk[0..n) are spread over the table, from a sample of
-// 32 groups of 64 neighbouring keys: at least three quarters of the sample have
-// a line of the table of their own.  Groups in ascending order and (direct
-// tables) groups within 4 MB of payloads count as not spread, since neighbours
-// in the column then share an XCD's L2.  (Three quarters: with half of the keys
-// equal four slices still gain 17%, eight lose 28%; with a fifth of them sorted
-// or equal both gain.)  All workgroups read the same sample and come to the same
-// answer.  seen: 2^kSeenLg bits of LDS; total: one word.
+// 32 groups of 64 neighbouring keys: at least `percent` of the sample have a
+// line of the table of their own.  Groups in ascending order and (direct tables)
+// groups within 4 MB of payloads count as not spread, since neighbours in the
+// column then share an XCD's L2.  All workgroups read the same sample and come
+// to the same answer.  seen: 2^kSeenLg bits of LDS; total: one word.
 // Called by the whole workgroup, ends with a barrier.
 constexpr uint32_t kSeenLg = 15;
 
 template <int BLOCK, int KIND>
 __device__ __forceinline__ bool keys_are_spread(const DevTable &t, const int32_t *__restrict__ fk, int64_t n,
-                                                uint32_t *seen, uint32_t *total) {
+                                                uint32_t percent, uint32_t *seen, uint32_t *total) {
     constexpr int W = BLOCK / kWave, kGroups = 32;
     const int w = (int)threadIdx.x / kWave;
     const uint32_t lane = lane_id();
@@ -626,7 +624,7 @@ __device__ __forceinline__ bool keys_are_spread(const DevTable &t, const int32_t
     const uint32_t sum = (uint32_t)wave_sum_u64(mine);
     if (lane == 0) atomicAdd(total, sum);
     __syncthreads();
-    const bool spread = 4u * *total >= 3u * (uint32_t)(groups * kWave);
+    const bool spread = 100u * *total >= percent * (uint32_t)(groups * kWave);
     __syncthreads();
     return spread;
 }
@@ -647,6 +645,13 @@ __global__ __launch_bounds__(BLOCK) void ht_probe_sliced_kernel(DevTable t, cons
     // unsliced: 2^18 keys 8-13 / 10-40, four slices 2^20 keys 10-16 / 11-40; eight
     // slices, 2^20 times mostly one key 24 / 12)
     constexpr int64_t kSampleFrom = int64_t(1) << (LG == 3 ? 18 : 20);
+    // percent of the sample that has to be spread: with a fifth of the keys sorted
+    // or equal slices gain, with half of them four slices of a linear table still
+    // do (2^27 keys into 16 MB, in us, unsliced / sliced: one key 968/807, sorted
+    // 1,121/744, Zipf 887/738; 8 MB 688/733, 788/609, 728/644), but not with probe
+    // payloads (1,029/1,156), of a direct table (8 MB sorted 807/982) or eight
+    // slices (32 MB one key 1,114/1,422)
+    constexpr uint32_t kSpread = kLinear && LG == 2 && !PP ? 45 : 75;
     __shared__ int32_t q_key[T::WAVES][kQ];
     __shared__ int32_t q_pv[PP ? T::WAVES : 1][PP ? kQ : 1];
     __shared__ int32_t r_key[kLinear ? T::WAVES : 1][kR];
@@ -800,7 +805,7 @@ __global__ __launch_bounds__(BLOCK) void ht_probe_sliced_kernel(DevTable t, cons
     };
     const int64_t stride = gridDim.x >> LG;
     static_assert(T::WAVES * kQ * 32 >= 1u << kSeenLg, "the sample's bits lie in the slice queues");
-    const bool sliced = n <= kSampleFrom || keys_are_spread<BLOCK, KIND>(t, fk, n, (uint32_t *)q_key, &total);
+    const bool sliced = n <= kSampleFrom || keys_are_spread<BLOCK, KIND>(t, fk, n, kSpread, (uint32_t *)q_key, &total);
     int64_t tile = sliced ? blockIdx.x >> LG : n_tiles;
     ProbeRegs<IPT, PP> ra, rb;
     if (tile < n_tiles) load(tile, ra);
