@@ -344,3 +344,32 @@ def test_scalar_totals_with_neighbouring_outputs(serving, block, ipt, nq):
     got = outs.cpu().numpy()
     for q, (year, d, qm) in enumerate(consts):
         assert int(got[q]) - q == q11_oracle(f, year, (d, d + 2), qm), (q, consts[q])
+
+
+@pytest.mark.parametrize("rows", [10_000, 50_000, 200_000])
+def test_shipped_shape_of_a_short_scalar_range(serving, rows):
+    """One Q1.1 query over a short range of rows, at the shipped table's shape:
+    exact, and no slower than at the long ranges' shape (3% for noise)."""
+    from paper_2003_01178_amd import autotune
+    announce("shared scan short scalar range", rows)
+    t, sv = serving
+    out, status = zeros(1, 1), cx.new_status()
+    consts = [(1994, 1, 24)]
+
+    def us():
+        return min(autotune.time_graph_ms(lambda s: sv.q11_scan.run([[]], out, 0, rows, status=status, stream=s))
+                   for _ in range(5)) * 1e3
+
+    try:
+        cx.tune_reset()
+        cx.tune_load(cx.os.path.join(cx._HERE, "tune", "gfx950.txt"))
+        cx.check_status(sv.run_q11_batch(consts, out, 0, rows))
+        f = q11_fact_of(t)
+        want = q11_oracle(datagen.Q11Fact(**{k: getattr(f, k)[:rows] for k in ("datekey", "discount", "quantity",
+                                                                               "price")}), 1994, (1, 3), 24)
+        assert int(out[0].item()) == want
+        shipped = us()
+        cx.tune_set(cx.K_SHARED_SCAN_SCALAR, 512, 8, 0)
+        assert shipped <= 1.03 * us()
+    finally:
+        cx.tune_reset()
