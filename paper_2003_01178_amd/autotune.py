@@ -135,6 +135,10 @@ def improves(kernel, n, rows, untuned_ms, others=(), reps=10):
     return all(time_ms(call, reps=reps) <= 1.02 * base for call, base in others)
 
 
+# Row ranges that a shared-scan pass is swept over: a clock segment of a large
+# served table, one of a small table, and a short range.
+SCAN_ROWS = (75_000_000, 4_000_000, 200_000)
+
 WINNERS = {}
 
 
@@ -256,8 +260,8 @@ def main(argv=None):
         report["groupby_2^26_7000"] = rows[:8]
 
     if "shared" in kernels:
-        # one 16-query pass per serving template over a 75M-row clock segment
-        n = 75_000_000
+        # one 16-query pass per serving template over each range of SCAN_ROWS
+        n = SCAN_ROWS[0]
         t = datagen.star_tables(n=n, workload=4, with_q11_columns=True)
         sv = queries.ServingTemplates(queries.StarSchema(t))
         del t
@@ -270,29 +274,22 @@ def main(argv=None):
 
         # grouped templates (the star template) and scalar ones (Q1.1) are
         # tuned separately: their passes differ in registers and LDS
-        def star_pass():
-            for o in outs_s:
-                o.zero_()
-            sv.star_scan.run([[] for _ in outs_s], outs_s, 0, n)
+        for kernel, name, scan, outs, st in ((cx.K_SHARED_SCAN, "star", sv.star_scan, outs_s, st_s),
+                                             (cx.K_SHARED_SCAN_SCALAR, "q11", sv.q11_scan, outs_q, st_q)):
+            found = []
+            for m in SCAN_ROWS:
+                def one_pass():
+                    for o in outs:
+                        o.zero_()
+                    scan.run([[] for _ in outs], outs, 0, m)
 
-        def q11_pass():
-            for o in outs_q:
-                o.zero_()
-            sv.q11_scan.run([[] for _ in outs_q], outs_q, 0, n)
-
-        # timed passes accumulate without the clears: each holds 16 queries' marshalling
-        rows = sweep(cx.K_SHARED_SCAN, n, star_pass, lambda: np.concatenate([o.cpu().numpy() for o in outs_s]),
-                     candidates=quick_vec if args.quick else None, gpcs=(0, 1, 2, 4), reps=args.reps, log=log,
-                     launch=lambda strm: sv.star_scan.run([[] for _ in outs_s], outs_s, 0, n, status=st_s,
-                                                          stream=strm))
-        assign(cx.K_SHARED_SCAN, [(n, rows[0][1:])])
-        report["shared_star_75M_16"] = rows[:8]
-        rows = sweep(cx.K_SHARED_SCAN_SCALAR, n, q11_pass, lambda: np.concatenate([o.cpu().numpy() for o in outs_q]),
-                     candidates=quick_vec if args.quick else None, gpcs=(0, 1, 2, 4), reps=args.reps, log=log,
-                     launch=lambda strm: sv.q11_scan.run([[] for _ in outs_q], outs_q, 0, n, status=st_q,
-                                                         stream=strm))
-        assign(cx.K_SHARED_SCAN_SCALAR, [(n, rows[0][1:])])
-        report["shared_q11_75M_16"] = rows[:8]
+                # timed passes accumulate without the clears: each holds 16 queries' marshalling
+                rows = sweep(kernel, m, one_pass, lambda: np.concatenate([o.cpu().numpy() for o in outs]),
+                             candidates=quick_vec if args.quick else None, gpcs=(0, 1, 2, 4), reps=args.reps, log=log,
+                             launch=lambda strm: scan.run([[] for _ in outs], outs, 0, m, status=st, stream=strm))
+                found.append((m, rows[0][1:]))
+                report[f"shared_{name}_{m}_16"] = rows[:8]
+            assign(kernel, found)
         del sv
         torch.cuda.empty_cache()
     if "radix" in kernels:

@@ -72,3 +72,11 @@ def test_an_entry_has_to_gain_and_not_to_slow_other_calls(untuned, monkeypatch, 
     monkeypatch.setattr(autotune, "time_ms", lambda call, reps: call())
     rows = [(winner, 512, 8, 0), (2.0, 256, 8, 0)]
     assert autotune.improves(cx.K_SELECT, 1 << 29, rows, 1.0, [(lambda: other, 1.0)]) == worth
+
+
+def test_shared_scans_are_swept_over_short_ranges_too(untuned):
+    """The shipped table has other shapes for short ranges; a sweep of the
+    long one alone would replace them."""
+    autotune.assign(cx.K_SHARED_SCAN_SCALAR, [(m, (256 << i, 8, 0)) for i, m in enumerate(autotune.SCAN_ROWS)])
+    shapes = {cx.tune_get(cx.K_SHARED_SCAN_SCALAR, n) for n in (10_000, 3_000_000, 75_000_000)}
+    assert len(shapes) == 3
