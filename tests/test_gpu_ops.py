@@ -476,13 +476,17 @@ def test_short_probe_of_a_direct_table_does_not_wait_for_its_copy(dim, other, ha
     out = torch.zeros(2, dtype=torch.int64, device="cuda")
     fk = torch.randint(0, dim, (1000,), device="cuda", dtype=torch.int32)
 
-    def us(keys):
+    def table(keys):
         key = torch.arange(keys, dtype=torch.int32, device="cuda")
         ht = cx.HashTable(cx.HT_DIRECT, keys, 0, keys - 1, has_payload=has_payload)
         cx.check_status(ht.build(key, key if has_payload else None))
-        return min(autotune.time_graph_ms(lambda s: ht.probe(fk, out=out, stream=s)) for _ in range(5)) * 1e3
+        return ht
 
-    assert us(dim) <= 1.05 * us(other)
+    tables, us = (table(dim), table(other)), ([], [])
+    for _ in range(5):
+        for ht, times in zip(tables, us):
+            times.append(autotune.time_graph_ms(lambda s: ht.probe(fk, out=out, stream=s)) * 1e3)
+    assert min(us[0]) <= 1.05 * min(us[1])
 
 
 @pytest.mark.parametrize("n", [4999, 5000])
